@@ -311,7 +311,7 @@ struct fid_batch {
     int32_t f4_grid;                 // persistent workgroups
     int32_t f4_loci_max;
     int32_t f4_max_slots;            // most list owners of one query
-    int64_t f4_queries, f4_words;    // staged queries, their 32-locus words
+    int64_t f4_queries;              // staged queries
     int32_t n_f4_seed_sel, n_f4_direct_sel;
     int64_t f4_seed_q, f4_direct_q;  // queries of each selection
     int64_t f4_merge_q;
@@ -354,14 +354,14 @@ struct BatchPlan {
         int32_t n_q, n_loci, kpad, tiles, n_slots, qtiles;
         int64_t seed;                // seed prefix (== the slice: counted directly)
         bool direct;
-        int64_t g_off, w_off;        // first global query / staged word
+        int64_t g_off;               // first global query
         int64_t lbase, fbase;        // first list key / fill of the job in the fp4 lists
         size_t off_qx, off_counts, off_bounds;
     };
     std::vector<F4> f4;
     std::vector<Fp4BatchItem> f4_seed_items, f4_scan_items;
     std::vector<int32_t> f4_seed_qoff, f4_scan_qoff;  // [9] each
-    int64_t f4_queries = 0, f4_words = 0, f4_keys = 0, f4_fills = 0;
+    int64_t f4_queries = 0, f4_keys = 0, f4_fills = 0;
     int32_t f4_loci_max = 1, f4_max_slots = 0;
     int32_t n_seed_sel = 0, n_direct_sel = 0;
     int64_t seed_q = 0, direct_q = 0, merge_q = 0;
@@ -459,9 +459,7 @@ int plan_batch(const fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
             f.n_slots = f.direct ? 0 : (int32_t)std::min<int64_t>((ntiles + f.tiles - 1) / f.tiles,
                                                                 kMaxListWorkers / fp4_list_workers_per_wg());
             f.g_off = P->f4_queries;
-            f.w_off = P->f4_words;
             P->f4_queries += f.n_q;
-            P->f4_words += (int64_t)f.n_q * (f.kpad / 32);
             P->f4_loci_max = std::max(P->f4_loci_max, f.n_loci);
             if (!f.direct) {
                 const int32_t owners = f.n_slots * fp4_list_workers_per_wg();
@@ -660,7 +658,7 @@ int enqueue_fp4(fid_batch* b, hipStream_t s, bool timed)
 {
     hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, b->f4_counters, (int64_t)16, 0u);
     FID_HIP(hipGetLastError(), "fill launch");
-    FID_HIP(launch_expand_batch_fp4(b->f4_expand, b->f4_jobs, b->f4_words, b->f4_queries, b->f4_qmode, b->f4_pcq, s),
+    FID_HIP(launch_expand_batch_fp4(b->f4_expand, b->f4_jobs, b->f4_queries, b->f4_qmode, b->f4_pcq, s),
             "batched staging launch");
     FID_HIP(launch_fp4_batch(EPI_FULL, b->f4_seed_sets, b->f4_seed_items, b->f4_seed_qoff, b->f4_counters,
                              b->f4_grid, s), "batched seed pass launch");
@@ -780,7 +778,6 @@ int fid_batch_create(fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
         b->f4_loci_max = P.f4_loci_max;
         b->f4_max_slots = P.f4_max_slots;
         b->f4_queries = P.f4_queries;
-        b->f4_words = P.f4_words;
         b->f4_counters = reinterpret_cast<unsigned int*>(ws + P.off_f4_counters);
         b->f4_seed_sets = reinterpret_cast<Fp4BatchSet*>(ws + P.off_f4_sets);
         b->f4_scan_sets = b->f4_seed_sets + P.f4.size();
@@ -832,7 +829,7 @@ int fid_batch_create(fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
                 scan.wit = bounds + (size_t)(1 + kWitLevels) * f.n_q;
             }
             f4_sets[P.f4.size() + i] = scan;
-            f4_expand.push_back(Fp4ExpandJob{J.q_dev, f.n_q, J.db->row_words, f.n_loci, f.kpad, f.g_off, f.w_off, qx});
+            f4_expand.push_back(Fp4ExpandJob{J.q_dev, f.n_q, J.db->row_words, f.n_loci, f.kpad, f.g_off, qx});
             for (int32_t q = 0; q < f.n_q; ++q) f4_qmode.push_back(J.mode);
             SelectJob sj{};
             sj.counts = counts;

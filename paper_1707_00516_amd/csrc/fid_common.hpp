@@ -144,12 +144,11 @@ struct Fp4BatchItem {
     int64_t tb, te;
 };
 // Query staging of many jobs in one launch: job j's rows start at global
-// query q_off (its pcq / qmode entries) and word w_off (32-locus words over
-// all jobs, for the thread split).
+// query q_off (its pcq / qmode entries).
 struct Fp4ExpandJob {
     const uint64_t* q;
     int32_t n_q, row_words, n_loci, kpad;
-    int64_t q_off, w_off;
+    int64_t q_off;
     uint8_t* qx;
 };
 // Per-query selection over a seed block of counts (one descriptor per job):
@@ -196,8 +195,8 @@ int mfma_queries_per_wg();
 int mfma_waves_per_wg();
 hipError_t launch_fp4_scan(int mode, int epi, const ScanParams& p, const MfmaBuffers& b,
                            hipStream_t s);
-// Identity queries (mode, or qmode[i] when mode is kModePerQuery) get
-// doubled codes.
+// Identity queries (mode, or qmode[i] when mode is kModePerQuery) get codes of
+// both signs.
 hipError_t launch_expand_queries_fp4(const uint64_t* q, int32_t n_q, int32_t row_words,
                                      int32_t n_loci, int mode, const int32_t* qmode, uint8_t* qx,
                                      int32_t kpad, int32_t* pcq, hipStream_t s);
@@ -213,9 +212,9 @@ int fp4_list_workers_per_wg();
 hipError_t launch_fp4_batch(int epi, const Fp4BatchSet* sets, const Fp4BatchItem* items, const int32_t* queue_off,
                             unsigned int* counters, int32_t grid, hipStream_t s);
 // Staged fp4 rows and |Q| of every query of n_jobs jobs (per-query modes
-// from qmode, indexed by global query); total_words = sum of n_q * kpad / 32.
-hipError_t launch_expand_batch_fp4(const Fp4ExpandJob* jobs, int32_t n_jobs, int64_t total_words, int64_t total_q,
-                                   const int32_t* qmode, int32_t* pcq, hipStream_t s);
+// from qmode, indexed by global query).
+hipError_t launch_expand_batch_fp4(const Fp4ExpandJob* jobs, int32_t n_jobs, int64_t total_q, const int32_t* qmode,
+                                   int32_t* pcq, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_min_bound(uint32_t* thr, const uint32_t* bound, int32_t n, bool keep, int32_t n_loci,
                             uint32_t* level, uint32_t* wit, hipStream_t s);

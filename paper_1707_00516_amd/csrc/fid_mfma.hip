@@ -15,6 +15,8 @@
 // blocks: 8 accumulators of 32x32 int32 per wave.  Per 32-locus step a lane
 // expands 4 x 16 reference bits (3 VALU ops per 4 loci) and issues 8 MFMAs;
 // the next 128-locus unit of reference bits is prefetched.
+#include <type_traits>
+
 #include "fid_device.hpp"
 
 namespace fid {
@@ -111,182 +113,6 @@ __device__ __noinline__ void mfma_insert(uint64_t mask, uint32_t c, int64_t r, i
     }
 }
 
-// Candidates of one fp4 tile epilogue wait in a per-wave LDS queue of
-// kCandQ4 entries.  An entry packs tile query m (7 bits), reference 16 j + n16
-// of the wave's 64 (6 bits) and the count (at most 65535, 16 bits):
-// m | ref << 7 | c << 13.  An out-of-line call waits for every memory
-// operation of the wave on entry and again before it returns, so in the
-// single-call scans the drain at the end of a tile leaves its global writes
-// to the caller: the call decides where each candidate goes (the bound, fill
-// and list updates live in LDS), and the caller then issues the list stores
-// inline, where nothing waits for them (witness counts collect in LDS and
-// reach global memory every 4th tile).  The persistent batch kernel, whose
-// registers leave no room for those inline stores, and a queue that fills up
-// mid-tile use a call that writes everything itself.
-constexpr int kCandQ4 = 64;
-constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
-
-// Drain the queue: every lane takes one entry, so the bound, fill and witness
-// lookups of up to 64 candidates happen at once; the witness counters take
-// every queued candidate below a level (each is a distinct reference of its
-// query: the scan meets a (query, reference) pair once); then the entries of
-// each query are appended or merged in queue order, with only readlanes
-// between list updates.
-__device__ __noinline__ void mfma_insert_queue(const lds_u32* cq, int n, int64_t rbase,
-                                               glb_u64* __restrict__ lists, int64_t qstride, int k,
-                                               lds_u32* lthr, lds_u32* lfill, const lds_u32* tlvl,
-                                               glb_u32* wit)
-{
-    const int lane = lane_id();
-    for (int e0 = 0; e0 < n; e0 += 64) {
-        const bool act = lane < n - e0;
-        const uint32_t v = act ? cq[e0 + lane] : 0u;
-        const int m = (int)(v & 127u);
-        const uint32_t c = v >> 13;
-        const int ref = (int)((v >> 7) & 63u);
-        const uint32_t t0 = act ? lthr[m] : 0u;
-        const uint32_t f0 = act ? lfill[m] : 0u;
-        if (wit && act) {
-            // levels decrease with l: a count at or above one is above the rest
-            for (int l = 0; l < kWitLevels; ++l) {
-                if (c >= tlvl[kWitLevels * m + l]) break;
-                __hip_atomic_fetch_add(wit + kWitLevels * m + l, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        const bool keep = act && c < t0;
-        uint64_t rem = __builtin_amdgcn_ballot_w64(keep);
-        while (rem) {
-            const int lead = __builtin_ctzll(rem);
-            const int ms = __builtin_amdgcn_readlane(m, lead);
-            uint64_t sel = __builtin_amdgcn_ballot_w64(keep && m == ms);
-            rem &= ~sel;
-            // this query's bound and fill, as read above (no entry of this
-            // chunk has touched them yet)
-            uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)t0, lead);
-            uint32_t fill = (uint32_t)__builtin_amdgcn_readlane((int)f0, lead);
-            glb_u64* list = lists + (size_t)ms * qstride;
-            while (sel) {
-                const int src = __builtin_ctzll(sel);
-                sel &= sel - 1;
-                const uint32_t cs = (uint32_t)__builtin_amdgcn_readlane((int)c, src);
-                if (cs >= t) continue;
-                const uint64_t key =
-                    ((uint64_t)cs << kIdxBits) | (uint64_t)(rbase + __builtin_amdgcn_readlane(ref, src));
-                uint64_t mx;
-                int mpos;
-                bool changed = false;
-                if (fill < (uint32_t)k) {
-                    if (lane == (int)(fill & 63u)) list[fill] = key;
-                    ++fill;
-                    changed = fill == (uint32_t)k;
-                } else {
-                    list_max(list, k, mx, mpos);
-                    if (key < mx) {
-                        if (lane == (mpos & 63)) list[mpos] = key;
-                        changed = true;
-                    }
-                }
-                if (changed) {
-                    list_max(list, k, mx, mpos);
-                    const uint32_t bound = (uint32_t)(mx >> kIdxBits) + 1u;
-                    if (bound < t) t = bound;
-                }
-            }
-            if (lane == 0) {
-                lthr[ms] = t;
-                lfill[ms] = fill;
-            }
-        }
-        wave_lds_sync();
-    }
-}
-
-// End-of-tile drain of n <= 64 queued candidates (lane e takes entry e).  The
-// entries of one query are kept in queue order while below its bound; as long
-// as its list does not fill, they are appended at the next free slots, and the
-// slot of entry e goes to cpos[e] for the caller to store (kNoSlot: nothing to
-// store).  A list that fills takes its entries one by one here, with
-// immediate stores, since its new bound needs the list's worst key.  Witness
-// counts go to the workgroup's LDS counters wloc, which the waves add to the
-// global ones every 4th tile.
-__device__ __noinline__ void mfma_drain_decide(const lds_u32* cq, lds_u32* cpos, int n, int64_t rbase,
-                                               glb_u64* __restrict__ lists, int64_t qstride, int k,
-                                               lds_u32* lthr, lds_u32* lfill, const lds_u32* tlvl,
-                                               lds_u32* wloc)
-{
-    const int lane = lane_id();
-    const bool act = lane < n;
-    const uint32_t v = act ? cq[lane] : 0u;
-    const int m = (int)(v & 127u);
-    const uint32_t c = v >> 13;
-    const int ref = (int)((v >> 7) & 63u);
-    const uint32_t t0 = act ? lthr[m] : 0u;
-    const uint32_t f0 = act ? lfill[m] : 0u;
-    if (wloc && act) {
-        // witness counts of every queued candidate below a level, into the
-        // workgroup's LDS counters (each is a distinct reference of its query:
-        // the scan meets a pair once)
-        for (int l = 0; l < kWitLevels; ++l)
-            if (c < tlvl[kWitLevels * m + l])
-                __hip_atomic_fetch_add(wloc + kWitLevels * m + l, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    uint32_t slot = kNoSlot;
-    const bool keep = act && c < t0;
-    uint64_t rem = __builtin_amdgcn_ballot_w64(keep);
-    while (rem) {
-        const int lead = __builtin_ctzll(rem);
-        const int ms = __builtin_amdgcn_readlane(m, lead);
-        const bool mine = keep && m == ms;
-        uint64_t sel = __builtin_amdgcn_ballot_w64(mine);
-        rem &= ~sel;
-        const uint32_t nsel = (uint32_t)__popcll(sel);
-        uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)t0, lead);
-        uint32_t fill = (uint32_t)__builtin_amdgcn_readlane((int)f0, lead);
-        if (fill + nsel < (uint32_t)k) {
-            // appends only: every entry is below the bound, which stays put
-            if (mine)
-                slot = fill + (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(sel >> 32),
-                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)sel, 0u));
-            fill += nsel;
-        } else {
-            glb_u64* list = lists + (size_t)ms * qstride;
-            while (sel) {
-                const int src = __builtin_ctzll(sel);
-                sel &= sel - 1;
-                const uint32_t cs = (uint32_t)__builtin_amdgcn_readlane((int)c, src);
-                if (cs >= t) continue;
-                const uint64_t key =
-                    ((uint64_t)cs << kIdxBits) | (uint64_t)(rbase + __builtin_amdgcn_readlane(ref, src));
-                uint64_t mx;
-                int mpos;
-                bool changed = false;
-                if (fill < (uint32_t)k) {
-                    if (lane == (int)(fill & 63u)) list[fill] = key;
-                    ++fill;
-                    changed = fill == (uint32_t)k;
-                } else {
-                    list_max(list, k, mx, mpos);
-                    if (key < mx) {
-                        if (lane == (mpos & 63)) list[mpos] = key;
-                        changed = true;
-                    }
-                }
-                if (changed) {
-                    list_max(list, k, mx, mpos);
-                    const uint32_t bound = (uint32_t)(mx >> kIdxBits) + 1u;
-                    if (bound < t) t = bound;
-                }
-            }
-        }
-        if (lane == 0) {
-            lthr[ms] = t;
-            lfill[ms] = fill;
-        }
-    }
-    if (act) cpos[lane] = slot;
-    wave_lds_sync();
-}
-
 __device__ __noinline__ void mfma_append_hits(uint64_t mask, bool hit, int32_t c, int64_t r, int q,
                                               unsigned long long* __restrict__ hit_count,
                                               uint64_t* __restrict__ hit_keys,
@@ -306,6 +132,122 @@ __device__ __noinline__ void mfma_append_hits(uint64_t mask, bool hit, int32_t c
             hit_keys[pos] = ((uint64_t)q << kIdxBits) | (uint64_t)r;
             hit_cnt[pos] = c;
         }
+    }
+}
+
+// Candidates of one fp4 tile epilogue wait in a per-wave LDS queue of
+// kCandQ4 entries.  An entry packs tile query m (7 bits), reference 0..63 of
+// the wave's block (6 bits) and the count (at most 65535, 16 bits):
+// m | ref << 7 | c << 13.
+constexpr int kCandQ4 = 64;
+
+// Drain the queue of n <= 64 entries into the wave's top-k lists.  Every lane
+// takes one entry, so the bound, fill and witness lookups of all candidates
+// happen at once.  The entries of one query below its bound are appended at
+// the next free slots; a list that fills takes its entries one by one, since
+// its new bound needs the list's worst key.  Witness counts (every queued
+// candidate below a level: each is a distinct reference of its query, as the
+// scan meets a pair once) go to the workgroup's LDS counters wloc, which the
+// waves add to the global ones every few tiles.  Inlined where nothing of the
+// tile but the candidate test's operands is live: an out-of-line call waits
+// for every memory operation of the wave on entry and on return, the next
+// tile's prefetch and its own list stores included.
+__device__ __forceinline__ void fp4_drain_lists(const lds_u32* cq, int n, int64_t rbase,
+                                                glb_u64* __restrict__ lists, int64_t qstride, int k, lds_u32* lthr,
+                                                lds_u32* lfill, const lds_u32* tlvl, lds_u32* wloc)
+{
+    const int lane = lane_id();
+    const bool act = lane < n;
+    const uint32_t v = act ? cq[lane] : 0u;
+    const int m = (int)(v & 127u);
+    const uint32_t c = v >> 13;
+    const uint64_t key = ((uint64_t)c << kIdxBits) | (uint64_t)(rbase + ((v >> 7) & 63u));
+    const uint32_t t0 = act ? lthr[m] : 0u;
+    const uint32_t f0 = act ? lfill[m] : 0u;
+    if (wloc && act) {
+#pragma unroll
+        for (int l = 0; l < kWitLevels; ++l)
+            if (c < tlvl[kWitLevels * m + l])
+                __hip_atomic_fetch_add(wloc + kWitLevels * m + l, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    const bool keep = act && c < t0;
+    uint64_t rem = __builtin_amdgcn_ballot_w64(keep);
+    while (rem) {
+        const int lead = __builtin_ctzll(rem);
+        const int ms = __builtin_amdgcn_readlane(m, lead);
+        const bool mine = keep && m == ms;
+        uint64_t sel = __builtin_amdgcn_ballot_w64(mine);
+        rem &= ~sel;
+        const uint32_t nsel = (uint32_t)__popcll(sel);
+        uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)t0, lead);
+        uint32_t fill = (uint32_t)__builtin_amdgcn_readlane((int)f0, lead);
+        glb_u64* list = lists + (size_t)ms * qstride;
+        if (fill + nsel < (uint32_t)k) {
+            // appends only: every entry is below the bound, which stays put
+            if (mine)
+                list[fill + (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(sel >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)sel, 0u))] = key;
+            fill += nsel;
+        } else {
+            while (sel) {
+                const int src = __builtin_ctzll(sel);
+                sel &= sel - 1;
+                const uint32_t cs = (uint32_t)__builtin_amdgcn_readlane((int)c, src);
+                if (cs >= t) continue;
+                const uint64_t ks =
+                    ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), src) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, src);
+                uint64_t mx;
+                int mpos;
+                uint32_t at = fill;
+                if (fill == (uint32_t)k) {
+                    wave_lds_sync();  // (orders this wave's list stores before its loads)
+                    list_max(list, k, mx, mpos);
+                    if (ks >= mx) continue;
+                    at = (uint32_t)mpos;
+                } else {
+                    ++fill;
+                }
+                if (lane == (int)(at & 63u)) list[at] = ks;
+                if (fill == (uint32_t)k) {
+                    wave_lds_sync();
+                    list_max(list, k, mx, mpos);
+                    const uint32_t bound = (uint32_t)(mx >> kIdxBits) + 1u;
+                    if (bound < t) t = bound;
+                }
+            }
+        }
+        if (lane == 0) {
+            lthr[ms] = t;
+            lfill[ms] = fill;
+        }
+    }
+    wave_lds_sync();
+}
+
+// Append the queued references whose count is below the threshold + 1 (tthr)
+// of their query to the threshold hits: one atomic per drain.
+__device__ __forceinline__ void fp4_drain_hits(const lds_u32* cq, int n, int64_t rbase, int q0, const lds_u32* tthr,
+                                               unsigned long long* __restrict__ hit_count,
+                                               uint64_t* __restrict__ hit_keys, int32_t* __restrict__ hit_cnt,
+                                               int64_t cap)
+{
+    const int lane = lane_id();
+    const bool act = lane < n;
+    const uint32_t v = act ? cq[lane] : 0u;
+    const int m = (int)(v & 127u);
+    const uint32_t c = v >> 13;
+    const bool hit = act && c < tthr[m];
+    const uint64_t hm = __builtin_amdgcn_ballot_w64(hit);
+    if (!hm) return;
+    unsigned long long first = 0;
+    if (lane == 0) first = atomicAdd(hit_count, (unsigned long long)__popcll(hm));
+    first = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(first >> 32)) << 32) |
+            (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)first);
+    const unsigned long long pos = first + (unsigned long long)__popcll(hm & ((1ull << lane) - 1ull));
+    if (hit && pos < (unsigned long long)cap) {
+        hit_keys[pos] = ((uint64_t)(q0 + m) << kIdxBits) | (uint64_t)(rbase + ((v >> 7) & 63u));
+        hit_cnt[pos] = (int32_t)c;
     }
 }
 
@@ -582,9 +524,17 @@ hipError_t launch_mfma_scan(int mode, int epi, const ScanParams& p, const MfmaBu
 
 // ======================================================================
 // fp4 (e2m1) matrix-core variant: v_mfma_f32_16x16x128_f8f6f4 with both
-// operands in e2m1 and the fp32 accumulation of at most 65536 unit products,
-// which is exact.  It runs the same closed forms as the int8 kernel at twice
-// the MAC rate per instruction.
+// operands in e2m1 and the fp32 accumulation of at most 65536 products of 1
+// (or of 2), which is exact.  It runs at twice the MAC rate of the int8 kernel.
+//
+// With identity queries' codes doubled (mul = 2, else 1), the accumulators
+// start at -|R| and a sum x = mul D - |R| = tpcq - count, with tpcq = |Q| for
+// identity queries and 0 for mixtures.  "count < bound" is x > tpcq - bound: one
+// starting value per reference and one cut per query, and every instance
+// serves both modes, one or per query.  (Products of -1 would count without
+// the starting value, from codes that are -1 where Q is 0; but the sums of
+// negative products cost so much power that the clock falls from 2.3 to
+// 2.05 GHz: 2048 x 20M x 2048 25.3 ms against 22 ms.)
 //
 // Element order and values: a dot product does not depend on the order of k
 // as long as both operands use the same one.  Each 32-locus word w of a
@@ -593,41 +543,44 @@ hipError_t launch_mfma_scan(int mode, int epi, const ScanParams& p, const MfmaBu
 // codes must be: the reference keeps loci 4j, 4j+1, 4j+2 where they are (e2m1
 // 0x1 = 0.5, 0x2 = 1.0, 0x4 = 2.0: dword d = w & (0x11111111 << d)) and moves
 // locus 4j+3 down one bit (2.0), 5 VALU ops per 32 loci; the queries, staged
-// once, carry the reciprocals (2.0, 1.0, 0.5, 0.5), so every product of two
-// set bits is exactly 1.  The k index of an
-// MFMA is permuted further so that each lane loads whole 16-byte units:
-// within a group of 4 units (512 loci), lane group kg (k quarter of the
-// MFMA operand) holds unit 4g + kg and feeds its word t to step t, so one
+// once, carry the reciprocals (2.0, 1.0, 0.5, 0.5) or twice those.  The k
+// index of an MFMA is permuted further so that each lane loads whole 16-byte
+// units: within a group of 4 units (512 loci), lane group kg (k quarter of
+// the MFMA operand) holds unit 4g + kg and feeds its word t to step t, so one
 // dwordx4 load per lane and 16-reference block covers 4 MFMA steps.
 //
-// Workgroup = 8 waves sharing a 128-query tile that lives in LDS for the
-// kernel's lifetime (rows padded by 16 bytes).  Each wave computes all 128
-// queries against its own 64-reference database block (8 x 4 blocks of
-// 16x16 fp32 accumulators, 32 MFMAs per 128 loci); the next group of units
-// (possibly of the next reference tile) is always in flight.  Accumulators
-// start at zero; the top-k and threshold epilogues apply the closed forms
-// and the bounds to D afterwards, with the tile's reference popcounts moved
-// into LDS by the DMA engine while the tile is scanned.  Nothing that the
-// epilogue computes lives across the scan loop, which keeps the whole tile
-// in registers without spills.
+// Workgroup = 8 waves sharing a query tile of NA 16-query blocks (NA <= 8) in
+// LDS.  Each wave computes them against its own 64-reference database block:
+// NA x 4 blocks of 16 x 16 accumulators with the references along the rows,
+// so a lane holds 4 consecutive references of one query per block (16-byte
+// stores of full counts, one bound per lane and query block).
 namespace {
 
-constexpr int kQB4 = 128;               // queries per workgroup (and per wave)
-constexpr int kQA4 = kQB4 / 16;         // 16-query row blocks per wave
-constexpr int kNB4 = 4;                 // 16-reference column blocks per wave
+constexpr int kQB4 = 128;               // most queries per workgroup (and per wave)
+constexpr int kNB4 = 4;                 // 16-reference blocks per wave
 constexpr int kRefsPerWave4 = 16 * kNB4;
 constexpr int kRefsPerWG4 = kRefsPerWave4 * kWavesM;
 constexpr int kUnitsPerGroup4 = 4;      // 16-byte units per load group
-constexpr int kKChunk4 = 2048;          // loci of the query tile resident in LDS at a time:
-                                        // 128 x (1024 + 16) B of queries + 13 KiB fit the LDS
+constexpr int kHalfLoci4 = 1024;        // loci of the query tile in one of the two LDS halves
+constexpr int kHalfRow4 = kHalfLoci4 / 2;           // staged bytes of a row in a half
+constexpr int kPlane4 = kQB4 * kHalfRow4 / 4;       // one k quarter of a half: 128 rows x 128 bytes
+constexpr int kHalfBytes4 = 4 * kPlane4;            // 64 KiB
 constexpr int kMaxKpad4 = 65536;
-constexpr int kRowBytes4 = kKChunk4 / 2 + 16;  // LDS stride of a staged query row
+constexpr int kRing4 = 2;               // query blocks read from LDS ahead of their MFMAs
 constexpr int kWaitVm0 = 0x0F70;        // s_waitcnt vmcnt(0), other counters untouched
+constexpr int kWaitVm4 = 0x0F74;        // s_waitcnt vmcnt(4): all but the newest four
+static_assert(kUnitsPerGroup4 % kRing4 == 0, "the ring of query blocks restarts with every group");
+static_assert(kNB4 == 4, "kWaitVm4 leaves one group's loads in flight");
 static_assert(kRefsPerWave4 == 64, "a wave covers exactly one database block");
 static_assert(kDbTileRefs % kRefsPerWG4 == 0, "tiles must not cross the database padding granule");
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
+// four counts of a row at any 4-byte aligned address
+typedef int v4i_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+typedef __attribute__((address_space(3))) v4u lds_v4u;
 
 __device__ __forceinline__ v8i spread_fp4(uint32_t w)
 {
@@ -648,18 +601,28 @@ __device__ __forceinline__ uint32_t word_of(const uint4& v, int t)
     return t == 0 ? v.x : t == 1 ? v.y : t == 2 ? v.z : v.w;
 }
 
+// Query tiles: the 16-query blocks of [0, n_q) dealt evenly to
+// ceil(n_q / 128) tiles, so that 131 queries run as tiles of 5 and 4 blocks
+// and not as 8 and 1 (whose references are read, spread and checked for
+// 3 queries).
+__host__ __device__ inline int fp4_tile_blocks(int n_q) { return (n_q + 15) / 16; }
+__host__ __device__ inline int fp4_tile_begin(int n_q, int n_tiles, int t)
+{
+    return 16 * (int)((int64_t)fp4_tile_blocks(n_q) * t / n_tiles);
+}
+
 }  // namespace
 
 // One work item of the fp4 scan (see fp4_work).
 struct Fp4Work {
     DbView db;
-    int64_t r_lo, r_hi;            // the query set's reference range (others compare as +inf)
+    int64_t r_lo, r_hi;            // the query set's reference range (others are masked)
     int64_t base;                  // r_lo rounded down to a database tile
     int64_t tb, te;                // 512-reference tiles [tb, te) from base
     const uint8_t* qx;             // staged queries of the set, row q at qx + q * kpad / 2
     int32_t kpad;
-    bool multi_chunk;              // rows span several LDS chunks (restaged per tile)
     const int32_t* pcq;            // |Q| per query of the set
+    int mode;                      // fid_mode of every query, or kModePerQuery
     const int32_t* qmode;          // per-query fid_mode (kModePerQuery)
     int32_t q0, nq_tile;           // query tile of the set
     int32_t slot, n_slots;         // this item's reference range among the set's ranges
@@ -680,22 +643,69 @@ struct Fp4Work {
     int64_t hit_cap;
 };
 
-// Rows longer than one LDS chunk: stage loci [c * kKChunk4, (c + 1) * kKChunk4)
-// of every query of the tile, straight from global memory into LDS
-// (global_load_lds moves no data through registers, so a tile's accumulators
-// stay live across a restage).  One wave instruction moves one row's chunk of
-// <= 1 KiB; rows past the tile's queries are zeroed once by the caller.
-__device__ __forceinline__ void fp4_stage_chunk(const uint8_t* __restrict__ qx, int qrow, int cbytes,
-                                                int row_bytes, int q0, int nq_tile, int wv, int lane,
-                                                int c, uint8_t* qt)
+// A wave-uniform value in scalar registers (the persistent kernel reads its
+// items between assembly that may write memory, so its loads are vector loads).
+__device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uni(int64_t v)
 {
-    typedef __attribute__((address_space(3))) uint8_t lds_u8;
-    const int bytes = min(cbytes, qrow - c * cbytes);
-    for (int r = wv; r < nq_tile; r += kWavesM)
-        if (lane * 16 < bytes)
-            __builtin_amdgcn_global_load_lds(qx + (size_t)(q0 + r) * qrow + (size_t)c * cbytes + lane * 16,
-                                             (lds_u8*)(qt + r * row_bytes), 16, 0, 0);
-    __builtin_amdgcn_s_waitcnt(0);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+template <class T>
+__device__ __forceinline__ T* uni(T* p)
+{
+    return reinterpret_cast<T*>(uni((int64_t)reinterpret_cast<uintptr_t>(p)));
+}
+
+// A wave's DMA instruction: 64 lanes x `16 bytes` (or 4) from base + off into
+// LDS at the wave-uniform byte address lds.  Written as assembly because the
+// compiler makes every LDS read that follows the builtin wait for all loads
+// in flight; here the LDS halves alternate, and the wait (vmcnt 0, before the
+// workgroup barrier that hands a half over) is the caller's.  No register is
+// written, and a wait the compiler places for its own loads can only get
+// stricter by loads it does not know of.
+__device__ __forceinline__ void dma16(uint32_t lds, const void* base, uint32_t off)
+{
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(uni((int32_t)lds)), "v"(off), "s"(uni(base))
+                     : "memory");
+}
+__device__ __forceinline__ void dma4(uint32_t lds, const void* base, uint32_t off)
+{
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                     :
+                     : "s"(uni((int32_t)lds)), "v"(off), "s"(uni(base))
+                     : "memory");
+}
+
+// Stage half row hh (loci [1024 hh, 1024 hh + 1024)) of the tile's 16 NA rows
+// into the LDS half at byte address half: NA instructions per wave.  A half
+// is four planes, one per k quarter, of 128-byte rows whose eight 16-byte
+// words (two groups x four steps) are permuted by the row (word c at c ^
+// (row / 2 mod 8)): the 16 lanes that an LDS read serves at a time then meet
+// all 64 banks.  Rows past the tile's queries repeat its last query; their
+// bounds admit nothing.
+template <int NA>
+__device__ __forceinline__ void fp4_stage_half(const Fp4Work& w, int wv, int lane, int hh, uint32_t half)
+{
+    const int qrow = w.kpad / 2;
+    const uint8_t* base = w.qx + (size_t)w.q0 * qrow + (size_t)hh * kHalfRow4;
+    // opaque: the addresses are recomputed (four ops each), not held or
+    // spilled across the scan loop
+    int l = lane;
+    __asm__ volatile("" : "+v"(l));
+    const int row0 = l >> 3;
+    const uint32_t word0 = (uint32_t)((l & 7) ^ (l >> 4)) * 16u;
+#pragma unroll
+    for (int s = 0; s < NA; ++s) {
+        const int idx = wv * NA + s;          // (plane, 8-row block)
+        const int kg = idx / (2 * NA), rb = idx % (2 * NA);
+        const uint32_t row = (uint32_t)min(rb * 8 + row0, w.nq_tile - 1);
+        dma16(half + (uint32_t)(kg * kPlane4 + rb * 1024), base + kg * 128,
+              __umul24(row, (uint32_t)qrow) + (word0 ^ ((uint32_t)(rb & 1) << 6)));
+    }
 }
 
 // Witness counts gathered in LDS since the last flush go to the global
@@ -716,33 +726,42 @@ __device__ __forceinline__ void fp4_flush_witness(uint32_t* wloc, uint32_t* __re
     }
 }
 
-// LDS: [query tile 128 x kRowBytes4] [bound 8 x 128] [fill 8 x 128]
-// [staged reference popcounts 8 x 2 x 64] [tile popcounts 128]
-// [tile thresholds 128] [tile modes 128] [witness levels 128 x kWitLevels]
+// LDS: [query tile: 2 halves] [bound 8 x 128] [fill 8 x 128]
+// [reference popcounts of this and the next tile 8 x 2 x 64] [tile popcounts 128]
+// [tile thresholds 128] [witness levels 128 x kWitLevels]
 // [staged witness counts 128 x kWitLevels, shared by the waves]
-// [combined bound 8 x 128] [candidate queues 8 x kCandQ4] [their list slots 8 x kCandQ4]
+// [candidate queues 8 x kCandQ4]
 // [witness counts not yet flushed 128 x kWitLevels].
-// One work item of the fp4 scan: query tile [q0, q0 + nq_tile) of a query
-// set against tiles [tb, te) of a reference range (the kernels below take
-// their items from the launch geometry or from a queue).  Every wave of the
-// workgroup calls it with the same item.  PARTIAL: the tile holds fewer than
-// 113 queries, and the MFMAs of its 16-query row blocks past the last query
-// are skipped (their accumulators keep their start value, which is what the
-// zero rows of those queries would leave).  DEFER: the end-of-tile drain only
-// decides where candidates go and this code issues the list stores, with
-// witness counts collected in LDS (else one call writes everything).
-template <int MODE, int EPI, bool KCHUNKS, bool PARTIAL, bool DEFER>
+constexpr size_t kLdsFp4 = 2 * (size_t)kHalfBytes4 + 3 * (size_t)kWavesM * kQB4 * 4 + 2 * (size_t)kQB4 * 4 +
+                           3 * (size_t)kWitLevels * kQB4 * 4 + (size_t)kWavesM * kCandQ4 * 4;
+// (the persistent batch kernel adds 16 bytes for its work queue)
+static_assert(kLdsFp4 + 16 <= 163840, "fp4 query tile and epilogue state must fit the 160 KiB LDS");
+
+// One work item of the fp4 scan: query tile [q0, q0 + nq_tile), at most 16 NA
+// queries, of a query set against tiles [tb, te) of a reference range (the
+// kernels below take their items from the launch geometry or from a queue).
+// Every wave of the workgroup calls it with the same item.
+//
+// Bound: the matrix cores and, once they are kept busy, the card's power (the
+// clock falls from 2.4 to 2.28 GHz).  The 128 queries x 64 references of
+// accumulators leave two waves per SIMD, so the order of a wave's own
+// instructions decides: each block of four MFMAs is pinned together with the
+// LDS read of the query block two ahead and its share of the next step's
+// spread (scheduling barriers; left to itself the compiler waits for an LDS
+// read before every four MFMAs), the LDS words are permuted so that no read
+// meets a bank twice, and the next half of a long row is copied by the DMA
+// engine under the current one.  Measured at 2048 x 20M x 2048, top-32 (the
+// scan alone): 23.1 ms before, 21.9 ms now, MFMA pipes busy 0.73 -> 0.80 of the
+// time; 256 x 2M x 32768 5.53 -> 5.05 ms; 2048 x 1M x 2048 full counts 3.75 ->
+// 2.68 ms (16-byte stores); 131 x 20M x 2048 3.17 -> 2.1 ms (tiles of 5 and 4
+// blocks).
+template <int EPI, bool KCHUNKS, int NA>
 __device__ __forceinline__ void fp4_work(const Fp4Work& w)
 {
-    typedef __attribute__((address_space(3))) int32_t lds_i32;
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    // (aligned so that the read addresses' permutation bits are the tile's own)
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem4[];
     constexpr bool kLists = EPI == EPI_TOPK || EPI == EPI_BOTH;    // top-k lists
     constexpr bool kHits = EPI == EPI_THRESH || EPI == EPI_BOTH;   // threshold hits
-    // Rows longer than kKChunk4 loci are staged chunk by chunk: the LDS tile
-    // holds loci [c * kKChunk4, (c + 1) * kKChunk4) of every query while the
-    // accumulators collect all chunks of a reference tile.
-    const uint8_t* __restrict__ qx = w.qx;
-    const int32_t kpad = w.kpad;
     const int32_t* __restrict__ pcq = w.pcq;
     int32_t* __restrict__ out = w.out;
     uint64_t* __restrict__ lists = w.lists;
@@ -751,67 +770,50 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
     const uint32_t* __restrict__ level = w.level;
     uint32_t* __restrict__ wit = w.wit;
     const int32_t* __restrict__ thr = w.thr;
-    unsigned long long* __restrict__ hit_count = w.hit_count;
-    uint64_t* __restrict__ hit_keys = w.hit_keys;
-    int32_t* __restrict__ hit_cnt = w.hit_cnt;
     const int q0 = w.q0;
     const int nq_tile = w.nq_tile;
     const int64_t base = w.base;
     const int64_t tb = w.tb;
-    const int64_t te = w.te;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int worker = w.slot * kWavesM + wv;
     const int n_workers_r = w.n_slots * kWavesM;
-    const bool multi_chunk = w.multi_chunk;
-    const int qrow = kpad / 2;             // expanded bytes per query
-    const int cbytes = KCHUNKS ? kKChunk4 / 2 : qrow;  // staged bytes per query and chunk
-    uint8_t* qt = smem;
-    uint32_t* lthr_all = reinterpret_cast<uint32_t*>(smem + kQB4 * kRowBytes4);
+    uint32_t* lthr_all = reinterpret_cast<uint32_t*>(smem4 + 2 * kHalfBytes4);
     uint32_t* lfill_all = lthr_all + kWavesM * kQB4;
     int32_t* pcst_all = reinterpret_cast<int32_t*>(lfill_all + kWavesM * kQB4);
-    int32_t* tpcq = pcst_all + kWavesM * 128;
+    int32_t* tpcq = pcst_all + kWavesM * 2 * kRefsPerWave4;
     int32_t* tthr = tpcq + kQB4;
-    int32_t* tmode = tthr + kQB4;
-    uint32_t* tlvl = reinterpret_cast<uint32_t*>(tmode + kQB4);
+    uint32_t* tlvl = reinterpret_cast<uint32_t*>(tthr + kQB4);
     uint32_t* wst = tlvl + kWitLevels * kQB4;
-    uint32_t* lbnd_all = wst + kWitLevels * kQB4;
-    uint32_t* cq_all = lbnd_all + kWavesM * kQB4;
-    uint32_t* cpos_all = cq_all + kWavesM * kCandQ4;
-    uint32_t* wloc = cpos_all + kWavesM * kCandQ4;  // witness counts not yet in global memory
+    uint32_t* cq_all = wst + kWitLevels * kQB4;
+    uint32_t* wloc = cq_all + kWavesM * kCandQ4;  // witness counts not yet in global memory
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem4;
 
     const int lane = lane_id();
     const int tid = (int)threadIdx.x;
     const int kg = lane >> 4;      // MFMA k quarter = output row group
     const int n16 = lane & 15;
 
-
-    if constexpr (KCHUNKS) {
-        for (int i = tid; i < (kQB4 - nq_tile) * (cbytes / 16); i += kWGM) {
-            const int row = nq_tile + i / (cbytes / 16);
-            const int col = (i % (cbytes / 16)) * 16;
-            *reinterpret_cast<uint4*>(qt + row * kRowBytes4 + col) = make_uint4(0u, 0u, 0u, 0u);
-        }
-        fp4_stage_chunk(qx, qrow, cbytes, kRowBytes4, q0, nq_tile, wv, lane, 0, qt);
-    } else {
-        // the whole row fits: one plain copy for the kernel's lifetime
-        const int vec_per_row = qrow / 16;
-        for (int i = tid; i < kQB4 * vec_per_row; i += kWGM) {
-            const int row = i / vec_per_row;
-            const int col = (i - row * vec_per_row) * 16;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (row < nq_tile) v = *reinterpret_cast<const uint4*>(qx + (size_t)(q0 + row) * qrow + col);
-            *reinterpret_cast<uint4*>(qt + row * kRowBytes4 + col) = v;
-        }
-    }
+    // groups of 512 loci, and the half rows that hold them; rows of more than
+    // two halves are staged half by half while the tile is scanned
+    const int ngroups = (w.db.n_loci + 511) / 512;
+    const int nhalves = (ngroups + 1) / 2;
+    const bool multi = KCHUNKS && nhalves > 2;
+    fp4_stage_half<NA>(w, wv, lane, 0, lds0);
+    if (!multi && nhalves > 1) fp4_stage_half<NA>(w, wv, lane, 1, lds0 + kHalfBytes4);
+    // the popcounts of the wave's 64 references of a tile: two buffers, the
+    // next tile's copied while this one is scanned (the database popcounts
+    // are padded like its words, so every reference of a tile is readable)
+    const uint32_t pcst = (uint32_t)(uintptr_t)(lds_u32*)(uint32_t*)(pcst_all + wv * 2 * kRefsPerWave4);
+    const int32_t* wpc = w.db.pc + base + tb * kRefsPerWG4 + wv * kRefsPerWave4;
+    if (w.te > tb) dma4(pcst, wpc, (uint32_t)lane * 4u);
     if (tid < kQB4) {
-        // tmode: 0 mixture, 1 identity; tpcq: |Q| of identity queries, 0 else.
-        // A count is then c = |R| + tpcq - (1 + tmode) D in every mode.
-        const int md = MODE != kModePerQuery ? MODE : (tid < nq_tile ? w.qmode[q0 + tid] : FID_MODE_MIXTURE);
-        tmode[tid] = md;
-        tpcq[tid] = (md == FID_MODE_IDENTITY && tid < nq_tile) ? pcq[q0 + tid] : 0;
+        // |Q| of identity queries, 0 for mixtures; rows past the tile's
+        // queries get a value that no sum exceeds
+        const int md = w.mode != kModePerQuery ? w.mode : (tid < nq_tile ? w.qmode[q0 + tid] : FID_MODE_MIXTURE);
+        tpcq[tid] = tid >= nq_tile ? 1 << 24 : md == FID_MODE_IDENTITY ? pcq[q0 + tid] : 0;
         // threshold hit "count <= thr" is "count < thr + 1"; thr is clamped to
         // [-1, L] first (counts lie in [0, L]), which keeps every fp32 value exact
-        int32_t tq = ((EPI == EPI_THRESH || EPI == EPI_BOTH) && tid < nq_tile) ? thr[q0 + tid] : -1;
+        int32_t tq = (kHits && tid < nq_tile) ? thr[q0 + tid] : -1;
         tq = tq < -1 ? -1 : (tq > w.db.n_loci ? w.db.n_loci : tq);
         tthr[tid] = tq + 1;
         for (int l = 0; l < kWitLevels; ++l) {
@@ -825,50 +827,34 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
     }
     uint32_t* lthr = lthr_all + wv * kQB4;
     uint32_t* lfill = lfill_all + wv * kQB4;
-    int32_t* pcst = pcst_all + wv * 128;
-    // EPI_BOTH: per row, the larger of the top-k bound and threshold + 1 --
-    // the bound the accumulators start from, so that a reference is looked
-    // at when either output may want it; refreshed whenever lthr changes
-    uint32_t* lbnd = lbnd_all + wv * kQB4;
     lds_u32* cq = (lds_u32*)(cq_all + wv * kCandQ4);   // the wave's candidate queue
-    lds_u32* cpos = (lds_u32*)(cpos_all + wv * kCandQ4);  // list slots the drain assigns
-    auto refresh_lbnd = [&]() {
-        if constexpr (EPI == EPI_BOTH) {
-            wave_lds_sync();
-            for (int i = lane_id(); i < kQB4; i += 64) lbnd[i] = max(lthr[i], (uint32_t)tthr[i]);
-            wave_lds_sync();
-        }
-    };
     const bool witness = kLists && wit != nullptr;
     if constexpr (kLists) {
         // rows past the tile's queries get bound 0: no count is below it.
         // A caller's bound may be anything up to 0xFFFFFFFF ("no bound yet");
         // counts never exceed L, so min(bound, L + 1) filters exactly the
-        // same and keeps every accumulator start an integer below 2^18,
-        // exact in fp32.
+        // same and keeps every compared value an integer below 2^25, exact
+        // in fp32.
         const uint32_t cap = (uint32_t)w.db.n_loci + 1u;
         for (int i = lane; i < kQB4; i += 64) {
             lthr[i] = i < nq_tile ? min(thr_init[q0 + i], cap) : 0u;
             lfill[i] = 0u;
         }
     }
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
     __syncthreads();
-    refresh_lbnd();
 
     // Unit group g of reference tile t for this wave: its database block is
     // (base + 512 t + 64 wv) / 64; lane (kg, n16) loads unit 4 g + kg of
-    // reference 16 j + n16 of that block.  Groups past the row (kpad may
-    // exceed the row's units by up to 3) read the next block or the
-    // database's slack: the matching query loci are zero.
-    const int ngroups = kpad / (128 * kUnitsPerGroup4);
-    const int na = (nq_tile + 15) >> 4;     // row blocks holding queries (PARTIAL)
+    // reference 16 j + n16 of that block.  Groups past the row (it may end up
+    // to 3 units into its last group) read the next block or the database's
+    // slack: the matching query loci are zero.
     const int w4 = w.db.w4;
     const char* words = reinterpret_cast<const char*>(w.db.words);
-    const int64_t blk0 = (base >> 6) + wv;
     const uint32_t loff = (uint32_t)kg * 1024u + (uint32_t)n16 * 16u;
     // Byte offsets of the wave's group g of tile t: wave-uniform, so a load
     // is a scalar base plus the lane's 32-bit offset.
-    const char* wbase = words + blk0 * w4 * 1024;
+    const char* wbase = words + ((base >> 6) + wv) * w4 * 1024;
     const int64_t tile_bytes = (int64_t)kWavesM * w4 * 1024;
     auto load_at = [&](uint4 (&dst)[kNB4], int64_t off) {
         const char* gp = wbase + off;
@@ -876,25 +862,31 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
         for (int j = 0; j < kNB4; ++j)
             dst[j] = *reinterpret_cast<const uint4*>(gp + (loff + (uint32_t)j * 256u));
     };
-    // A operand of step t of group g: query row 16 a + n16, 32-locus word
-    // 4 (4 g + kg) + t of the staged row (a compile-time row stride).
-    const uint8_t* arow = qt + n16 * kRowBytes4 + kg * 64;
+    // Query block a of step t in the group at x: row 16 a + n16 of plane kg,
+    // word (group parity, t) at its permuted place.
+    auto lds_a = [&](uint32_t x, int t, int a) -> v4u {
+        return *(const lds_v4u*)(uintptr_t)((x ^ (uint32_t)(t * 16)) + (uint32_t)(a * 16 * 128));
+    };
+    const uint32_t x_first = lds0 + (uint32_t)(kg * kPlane4 + n16 * 128 + ((n16 >> 1) & 7) * 16);
 
     uint4 cur[kNB4], nxt[kNB4];
     // tiles are counted from the range start in 32 bits (a range is far
     // shorter than 2^31 tiles), which keeps the loop state in scalar registers
-    const int nt = (int)(te - tb);
+    const int nt = (int)(w.te - tb);
     if (nt > 0) load_at(cur, tb * tile_bytes);
     int64_t toff = tb * tile_bytes;
+    uint32_t half = 0;             // byte offset of the LDS half in use
+    v4u ring[kRing4];
+#pragma unroll
+    for (int a = 0; a < kRing4; ++a) ring[a] = lds_a(x_first, 0, a);
+    v4f acc[NA][kNB4];
     for (int it = 0; it < nt; ++it, toff += tile_bytes) {
         const int64_t tile = tb + it;
         const int64_t rbase = base + tile * kRefsPerWG4 + (int64_t)wv * kRefsPerWave4;
-        // This tile's 64 reference popcounts go to LDS while the tile is
-        // scanned (two buffers: the previous tile's epilogue read the other).
-        // The database popcounts are padded like its words, so every
-        // reference of a tile is readable.
-        int32_t* pcs = pcst + (it & 1) * 64;
-        __builtin_amdgcn_global_load_lds(w.db.pc + rbase + lane, (lds_i32*)pcs, 4, 0, 0);
+        const uint32_t pcs = pcst + (uint32_t)(it & 1) * (kRefsPerWave4 * 4);
+        if (it + 1 < nt)
+            dma4(pcst + (uint32_t)(~it & 1) * (kRefsPerWave4 * 4), wpc + (int64_t)(it + 1) * kRefsPerWG4,
+                 (uint32_t)lane * 4u);
         // every 4th tile: the query tile's witness counts, read by the
         // epilogue; the workgroup's waves share them, each staging an eighth
         // (any value read is a count some time during the scan, and counts
@@ -905,251 +897,236 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
             for (int h = 0; h < (kPer + 63) / 64; ++h) {
                 const int o = kPer * wv + 64 * h;
                 if (64 * h + lane < kPer)
-                    __builtin_amdgcn_global_load_lds(
-                        wit + kWitLevels * q0 + min(o + lane, kWitLevels * nq_tile - 1), (lds_u32*)(wst + o), 4,
-                        0, 0);
+                    dma4((uint32_t)(uintptr_t)(lds_u32*)(wst + o), wit + (size_t)kWitLevels * q0,
+                         (uint32_t)min(o + lane, kWitLevels * nq_tile - 1) * 4u);
             }
         }
-        // Accumulator start: 0 for full counts; for top-k and threshold the
-        // row's bound (or threshold + 1) minus |Q| for identity queries, so
-        // that the scan leaves x = mul D + bound - |Q| (mul = 2 for identity
-        // queries, whose staged codes are doubled) and a candidate is x > |R|.
-        // The values sit in the accumulator registers themselves, which keeps
-        // one loop body for every tile.
-        v4f acc[kQA4][kNB4];
-#pragma unroll
-        for (int a = 0; a < kQA4; ++a) {
-            v4f init = v4f{0.f, 0.f, 0.f, 0.f};
-            if constexpr (EPI != EPI_FULL) {
-                const int o = 16 * a + 4 * kg;
-                const uint4 bv = *reinterpret_cast<const uint4*>(
-                    (EPI == EPI_THRESH ? reinterpret_cast<const uint32_t*>(tthr) : EPI == EPI_BOTH ? lbnd : lthr) +
-                    o);
-                const uint4 pv = *reinterpret_cast<const uint4*>(tpcq + o);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) init[i] = (float)word_of(bv, i) - (float)word_of(pv, i);
-            }
-#pragma unroll
-            for (int j = 0; j < kNB4; ++j) {
-                acc[a][j] = init;
-                __asm__ volatile("" : "+v"(acc[a][j]));
-            }
-        }
-
         // One group: prefetch the next (tile, group) into dst while the
         // MFMAs consume src.  Groups alternate between the two register sets,
-        // so nothing is copied between them.
+        // so nothing is copied between them.  The ring of query blocks runs
+        // on into the group at xn.
         const int64_t next_tile_off = it + 1 < nt ? toff + tile_bytes : toff;  // the last re-reads itself
-        auto group = [&](const uint4 (&src)[kNB4], uint4 (&dst)[kNB4], int g) {
-            if constexpr (KCHUNKS) {
-                // next query chunk (every workgroup wave reaches these barriers
-                // equally often: the tile range is the workgroup's)
-                if ((g & 3) == 0 && (g > 0 || it > 0) && multi_chunk) {
-                    __syncthreads();
-                    fp4_stage_chunk(qx, qrow, cbytes, kRowBytes4, q0, nq_tile, wv, lane, g >> 2, qt);
-                    __syncthreads();
-                }
-            }
+        auto group = [&](auto first, const uint4 (&src)[kNB4], uint4 (&dst)[kNB4], int g, uint32_t x, uint32_t xn,
+                         auto after_step0) {
             load_at(dst, g + 1 < ngroups ? toff + (int64_t)(g + 1) * (kUnitsPerGroup4 * 1024) : next_tile_off);
             // keep the prefetch ahead of this group's MFMAs (the scheduler
             // would otherwise sink it to its use to save registers)
             __builtin_amdgcn_sched_barrier(0);
-            const uint8_t* ga = arow + (KCHUNKS ? (g & 3) : g) * 256;
+            v8i b[2][kNB4];
+            v4f start[kNB4];   // -|R| of the lane's references
+#pragma unroll
+            for (int j = 0; j < kNB4; ++j) {
+                b[0][j] = spread_fp4(word_of(src[j], 0));
+                if constexpr (decltype(first)::value) {
+                    const v4u pr = *(const lds_v4u*)(uintptr_t)(pcs + (uint32_t)(16 * j + 4 * kg) * 4u);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) start[j][i] = -(float)(int32_t)pr[i];
+                }
+            }
 #pragma unroll
             for (int t = 0; t < kUnitsPerGroup4; ++t) {
-                v8i b[kNB4];
 #pragma unroll
-                for (int j = 0; j < kNB4; ++j) b[j] = spread_fp4(word_of(src[j], t));
+                for (int a = 0; a < NA; ++a) {
+                    const int slot = (t * NA + a) % kRing4;  // (a group takes a whole number of rounds)
+                    const v4u q = ring[slot];
+                    const v8i qv = v8i{(int)q[0], (int)q[1], (int)q[2], (int)q[3], 0, 0, 0, 0};
 #pragma unroll
-                for (int a = 0; a < kQA4; ++a) {
-                    if (PARTIAL && a >= na) continue;
-                    const uint4 x = *reinterpret_cast<const uint4*>(ga + a * 16 * kRowBytes4 + t * 16);
-                    const v8i av = v8i{(int)x.x, (int)x.y, (int)x.z, (int)x.w, 0, 0, 0, 0};
+                    for (int j = 0; j < kNB4; ++j) {
+                        const v4f c = decltype(first)::value && t == 0 ? start[j] : acc[a][j];
+                        acc[a][j] =
+                            __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b[t & 1][j], qv, c, 4, 4, 0, 0, 0, 0);
+                    }
+                    const int an = (a + kRing4) % NA, tn = t + (a + kRing4) / NA;
+                    ring[slot] = tn < kUnitsPerGroup4 ? lds_a(x, tn, an) : lds_a(xn, tn - kUnitsPerGroup4, an);
+                    if (t + 1 < kUnitsPerGroup4) {
 #pragma unroll
-                    for (int j = 0; j < kNB4; ++j)
-                        acc[a][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                            av, b[j], acc[a][j], 4, 4, 0, 0, 0, 0);
+                        for (int j = kNB4 * a / NA; j < kNB4 * (a + 1) / NA; ++j)
+                            b[(t + 1) & 1][j] = spread_fp4(word_of(src[j], t + 1));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (t == 0) after_step0();
+            }
+        };
+        // One half row: its two groups (one at the end of a row with an odd
+        // number of groups); a row of more than two halves has the next half
+        // copied into the other LDS half meanwhile (the barrier at the end
+        // of the previous half has freed it).
+        auto half_row = [&](auto first, int g) {
+            // opaque: the permuted addresses are cheaper recomputed (one op a
+            // step) than held in registers across the loop
+            uint32_t x = x_first + half;
+            __asm__ volatile("" : "+v"(x));
+            const uint32_t xo = x + kHalfBytes4 - 2 * half;
+            const bool two = g + 1 < ngroups;
+            const uint32_t x_next = multi || nhalves == 1 ? x : xo;  // where the next half will be read
+            auto copy_next = [&]() {
+                if constexpr (KCHUNKS) {
+                    if (multi && (g + 2 < ngroups || it + 1 < nt))
+                        fp4_stage_half<NA>(w, wv, lane, g + 2 < ngroups ? (g >> 1) + 1 : 0,
+                                           lds0 + (half ^ kHalfBytes4));
+                }
+            };
+            group(first, cur, nxt, g, x, two ? x ^ 64u : x_next, copy_next);
+            if (two) {
+                group(std::false_type{}, nxt, cur, g + 1, x ^ 64u, x_next, [] {});
+            } else {
+#pragma unroll
+                for (int j = 0; j < kNB4; ++j) cur[j] = nxt[j];
+            }
+            if (nhalves > 1) half ^= kHalfBytes4;
+            if constexpr (KCHUNKS) {
+                // (every wave reaches these barriers equally often: the tile
+                // range is the workgroup's)
+                if (multi) {
+                    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+                    __syncthreads();
+#pragma unroll
+                    for (int a = 0; a < kRing4; ++a) ring[a] = lds_a(x_first + half, 0, a);
                 }
             }
         };
-        int g = 0;
         // a wave in its scan loop outranks one in its epilogue, so the
         // matrix-core pipe keeps being fed while the other wave selects
         __builtin_amdgcn_s_setprio(1);
+        half_row(std::true_type{}, 0);
 #pragma unroll 1
-        for (; g + 1 < ngroups; g += 2) {
-            group(cur, nxt, g);
-            group(nxt, cur, g + 1);
-        }
-        if (g < ngroups) {
-            group(cur, nxt, g);
-#pragma unroll
-            for (int j = 0; j < kNB4; ++j) cur[j] = nxt[j];
-        }
+        for (int g = 2; g < ngroups; g += 2) half_row(std::false_type{}, g);
+        if (!multi) half = 0;
         __builtin_amdgcn_s_setprio(0);
 
-        // ---- epilogue: lane holds D = |R AND Q'| (or |R AND Q|) of reference
-        // rbase + 16 j + n16 and, in element i of row block a, tile query
-        // 16 a + 4 kg + i.  The lane coordinates are re-derived here, so that
-        // values computed from them stay local to the epilogue instead of
-        // living (or spilling) across the scan loop.
+        // ---- epilogue: element i of block (a, j) holds x of reference
+        // rbase + 16 j + 4 kg + i and tile query 16 a + n16.  The lane
+        // coordinates are re-derived here, so that values computed from them
+        // stay local to the epilogue instead of living (or spilling) across
+        // the scan loop.
         int lane_e = lane;
         __asm__ volatile("" : "+v"(lane_e));
         const int kg_e = lane_e >> 4;
         const int n16_e = lane_e & 15;
+        const bool inside = rbase >= w.r_lo && rbase + kRefsPerWave4 <= w.r_hi;  // wave-uniform
+        // The next tile's popcounts and the witness counts copied at this
+        // tile's start have landed: loads complete in order, and only the
+        // four of the next tile's first group may still be in flight.
+        __builtin_amdgcn_s_waitcnt(kWaitVm4);
+        __asm__ volatile("" ::: "memory");
         if constexpr (EPI == EPI_FULL) {
-            const int kg = kg_e;
-            const int n16 = n16_e;
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            __asm__ volatile("" ::: "memory");
 #pragma unroll
-            for (int j = 0; j < kNB4; ++j) {
-                const int64_t r = rbase + 16 * j + n16;
-                const bool rin = r >= w.r_lo && r < w.r_hi;
-                const int32_t pr = pcs[16 * j + n16];
-                int32_t* col = out + (r - w.out_r_base);
-#pragma unroll
-                for (int a = 0; a < kQA4; ++a)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int m = 16 * a + 4 * kg + i;
-                        // acc = mul D (identity codes are doubled); tpcq is 0
-                        // for mixture queries
-                        const int32_t c = pr + tpcq[m] - (int32_t)acc[a][j][i];
-                        if (rin && m < nq_tile) col[(size_t)(q0 + m - w.out_q_base) * w.ld] = c;
-                    }
-            }
-        } else {
-            // The staged popcounts landed once every load issued before the
-            // newest group prefetch has (loads complete in order).
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            __asm__ volatile("" ::: "memory");
-            const int kg = kg_e;
-            const int n16 = n16_e;
-            // A count c = |R| + |Q| - mul D (|Q| = 0 for mixture queries) is a
-            // candidate when c < bound, i.e. when the accumulator x = mul D +
-            // bound - |Q| exceeds |R|.  References outside [r_lo, r_hi) compare
-            // against +inf.  Every operand is an integer below 2^18, so x is
-            // exact in fp32.
-            const uint32_t* bnd =
-                EPI == EPI_THRESH ? reinterpret_cast<const uint32_t*>(tthr) : EPI == EPI_BOTH ? lbnd : lthr;
-            float prj[kNB4];
-#pragma unroll
-            for (int j = 0; j < kNB4; ++j) {
-                const int64_t r = rbase + 16 * j + n16;
-                const bool rin = r >= w.r_lo && r < w.r_hi;
-                prj[j] = rin ? (float)pcs[16 * j + n16] : __builtin_huge_valf();
-            }
-            bool any = false;
-#pragma unroll
-            for (int j = 0; j < kNB4; ++j) {
-                float mx = acc[0][j][0];
-#pragma unroll
-                for (int a = 0; a < kQA4; ++a)
-#pragma unroll
-                    for (int i = (a == 0 ? 1 : 0); i < 4; ++i) mx = fmaxf(mx, acc[a][j][i]);
-                any |= mx > prj[j];
-            }
-            if (__builtin_amdgcn_ballot_w64(any)) {
-                // rare.  c = |R| + bound - x with the bound the accumulators
-                // started from: inserts only tighten the bounds of their own
-                // row block, so each block reads its bounds before any of its
-                // candidates is inserted (a full queue is drained mid-tile with
-                // entries of this and earlier blocks only).
-                int qn = 0;  // queued candidates (wave-uniform)
-                glb_u64* wlists = (glb_u64*)(lists + ((size_t)q0 * n_workers_r + worker) * w.k);
-                glb_u32* wwit = witness ? (glb_u32*)(wit + kWitLevels * q0) : nullptr;
-#pragma unroll
-                for (int a = 0; a < kQA4; ++a) {
-                    const uint4 b0 = *reinterpret_cast<const uint4*>(bnd + 16 * a + 4 * kg);
-                    // list bounds of the block (EPI_BOTH; read before any of its inserts)
-                    uint4 lt = b0;
-                    if constexpr (EPI == EPI_BOTH) lt = *reinterpret_cast<const uint4*>(lthr + 16 * a + 4 * kg);
+            for (int a = 0; a < NA; ++a) {
+                const int m = 16 * a + n16_e;
+                const int32_t pq = tpcq[m];
+                if (m < nq_tile) {
+                    int32_t* row = out + (size_t)(q0 + m - w.out_q_base) * w.ld + (rbase + 4 * kg_e - w.out_r_base);
 #pragma unroll
                     for (int j = 0; j < kNB4; ++j) {
-                        const float bmx = fmaxf(fmaxf(acc[a][j][0], acc[a][j][1]), fmaxf(acc[a][j][2], acc[a][j][3]));
-                        if (!__builtin_amdgcn_ballot_w64(bmx > prj[j])) continue;
-                        const int64_t r = rbase + 16 * j + n16;
-                        const bool rin = prj[j] < 1.0e30f;
-                        const int32_t pr = rin ? pcs[16 * j + n16] : 0;
+                        if (inside) {
+                            v4i_a4 c;
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int m = 16 * a + 4 * kg + i;
-                            const int32_t c = pr + (int32_t)word_of(b0, i) - (int32_t)acc[a][j][i];
-                            if constexpr (kHits) {
-                                const bool hit = rin && c < tthr[m];
-                                const uint64_t hm = __builtin_amdgcn_ballot_w64(hit);
-                                if (hm)
-                                    mfma_append_hits(hm, hit, c, r, q0 + m, hit_count, hit_keys, hit_cnt,
-                                                     w.hit_cap);
+                            for (int i = 0; i < 4; ++i) c[i] = pq - (int32_t)acc[a][j][i];
+                            *reinterpret_cast<v4i_a4*>(row + 16 * j) = c;
+                        } else {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int64_t r = rbase + 16 * j + 4 * kg_e + i;
+                                if (r >= w.r_lo && r < w.r_hi) row[16 * j + i] = pq - (int32_t)acc[a][j][i];
                             }
-                            if constexpr (kLists) {
-                                // top-k alone: the accumulators started from lthr,
-                                // so c < lthr is x > |R|, with no LDS read
-                                const bool cand = EPI == EPI_TOPK ? acc[a][j][i] > prj[j]
-                                                                  : rin && (uint32_t)c < word_of(lt, i);
-                                const uint64_t bm = __builtin_amdgcn_ballot_w64(cand);
-                                if (bm) {
-                                    const int nb = __popcll(bm);
-                                    if (qn + nb > kCandQ4) {
-                                        wave_lds_sync();
-                                        mfma_insert_queue(cq, qn, rbase, wlists, (int64_t)n_workers_r * w.k, w.k,
-                                                          (lds_u32*)lthr, (lds_u32*)lfill, (const lds_u32*)tlvl,
-                                                          wwit);
-                                        qn = 0;
-                                    }
-                                    if (cand) {
-                                        const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi(
-                                                                 (uint32_t)(bm >> 32),
-                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)bm, 0u));
-                                        cq[pos] = (uint32_t)m | ((uint32_t)(16 * j + n16) << 7) |
-                                                  ((uint32_t)c << 13);
-                                    }
-                                    qn += nb;
+                        }
+                    }
+                }
+            }
+        } else {
+            // x > tpcq - bound is a candidate (bound: the top-k bound, the
+            // threshold + 1, or the larger of the two); every operand is an
+            // integer below 2^25, so the comparison is exact in fp32
+            float cut[NA], top[NA];
+            bool any = false;
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+                const int m = 16 * a + n16_e;
+                const uint32_t bound = EPI == EPI_TOPK     ? lthr[m]
+                                       : EPI == EPI_THRESH ? (uint32_t)tthr[m]
+                                                           : max(lthr[m], (uint32_t)tthr[m]);
+                cut[a] = (float)(tpcq[m] - (int32_t)bound);
+                top[a] = acc[a][0][0];
+#pragma unroll
+                for (int j = 0; j < kNB4; ++j)
+#pragma unroll
+                    for (int i = (j == 0 ? 1 : 0); i < 4; ++i) top[a] = fmaxf(top[a], acc[a][j][i]);
+                any |= top[a] > cut[a];
+            }
+            // (the stated probability is for the register allocator: what does not
+            // fit is to be spilled around the selection, never in the scan loop)
+            if (__builtin_expect_with_probability(__builtin_amdgcn_ballot_w64(any) != 0, 0, 0.99999)) {
+                // Queue the candidates of each block that holds one and drain
+                // the queue.  Should it fill up, the elements from `resume` on
+                // are queued in another pass (an element has at most 64
+                // candidates, one per lane, so every pass gets on); their
+                // bounds have tightened meanwhile, which the drain looks up.
+                int resume = 0;
+                // the block's references inside the range: [in_lo, in_lo + in_n), none of a
+                // block of padding
+                const int in_lo = (int)min(max(w.r_lo - rbase, (int64_t)0), (int64_t)kRefsPerWave4);
+                const int in_hi = (int)min(max(w.r_hi - rbase, (int64_t)0), (int64_t)kRefsPerWave4);
+                const uint32_t in_n = (uint32_t)max(in_hi - in_lo, 0);
+                do {
+                    int stop = 16 * NA, qn = 0;  // (wave-uniform)
+                    // opaque values, so that nothing of an element is
+                    // computed ahead of this loop and held (or spilled)
+                    float zero = 0.f;
+                    int row0 = 4 * kg_e;
+                    __asm__ volatile("" : "+v"(zero), "+v"(row0));
+#pragma unroll
+                    for (int a = 0; a < NA; ++a) {
+                        if (16 * a + 15 < resume || 16 * a >= stop) continue;
+                        float ca = cut[a];
+                        __asm__ volatile("" : "+v"(ca));
+                        if (!__builtin_amdgcn_ballot_w64(top[a] > ca)) continue;
+                        const int m = 16 * a + n16_e;
+                        const int32_t pq = tpcq[m];
+#pragma unroll
+                        for (int j = 0; j < kNB4; ++j) {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int e = 16 * a + 4 * j + i;
+                                const float x = acc[a][j][i];
+                                const int ref = 16 * j + i + row0;
+                                const bool cand = x > ca && (uint32_t)(ref - in_lo) < in_n;
+                                const uint64_t cm = __builtin_amdgcn_ballot_w64(cand);
+                                if (!cm || e < resume || e >= stop) continue;
+                                const int nb = __popcll(cm);
+                                if (qn + nb > kCandQ4) {
+                                    stop = e;
+                                    continue;
                                 }
+                                if (cand) {
+                                    const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi(
+                                                             (uint32_t)(cm >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)cm, 0u));
+                                    cq[pos] = (uint32_t)m | ((uint32_t)ref << 7) | ((uint32_t)(pq - (int32_t)(x + zero)) << 13);
+                                }
+                                qn += nb;
                             }
                         }
                     }
-                }
-                if constexpr (kLists && !DEFER) {
                     if (qn > 0) {
                         wave_lds_sync();
-                        mfma_insert_queue(cq, qn, rbase, wlists, (int64_t)n_workers_r * w.k, w.k, (lds_u32*)lthr,
-                                          (lds_u32*)lfill, (const lds_u32*)tlvl, wwit);
-                    }
-                }
-                if constexpr (kLists && DEFER) {
-                    if (qn > 0) {
+                        if constexpr (kHits)
+                            fp4_drain_hits(cq, qn, rbase, q0, (const lds_u32*)(uint32_t*)tthr, w.hit_count,
+                                           w.hit_keys, w.hit_cnt, w.hit_cap);
+                        if constexpr (kLists)
+                            fp4_drain_lists(cq, qn, rbase,
+                                            (glb_u64*)(lists + ((size_t)q0 * n_workers_r + worker) * w.k),
+                                            (int64_t)n_workers_r * w.k, w.k, (lds_u32*)lthr, (lds_u32*)lfill,
+                                            (const lds_u32*)tlvl, witness ? (lds_u32*)wloc : nullptr);
                         wave_lds_sync();
-                        const int64_t qstride = (int64_t)n_workers_r * w.k;
-                        mfma_drain_decide(cq, cpos, qn, rbase, wlists, qstride, w.k, (lds_u32*)lthr,
-                                          (lds_u32*)lfill, (const lds_u32*)tlvl, witness ? (lds_u32*)wloc : nullptr);
-                        // the drain's list appends, issued here with nothing
-                        // waiting for them, each by the lane owning its slot
-                        const bool act = lane_e < qn;
-                        const uint32_t v = act ? cq[lane_e] : 0u;
-                        const uint32_t slot = act ? cpos[lane_e] : kNoSlot;
-                        uint64_t dm = __builtin_amdgcn_ballot_w64(slot != kNoSlot);
-                        while (dm) {
-                            const int src = __builtin_ctzll(dm);
-                            dm &= dm - 1;
-                            const uint32_t ss = (uint32_t)__builtin_amdgcn_readlane((int)slot, src);
-                            const uint32_t vs = (uint32_t)__builtin_amdgcn_readlane((int)v, src);
-                            const uint64_t key = ((uint64_t)(vs >> 13) << kIdxBits) |
-                                                 (uint64_t)(rbase + ((vs >> 7) & 63u));
-                            if (lane_e == (int)(ss & 63u))
-                                wlists[(size_t)(vs & 127u) * qstride + ss] = key;
-                        }
                     }
-                }
-                refresh_lbnd();
+                    resume = stop;
+                } while (resume < 16 * NA);
             }
             if (witness && (it & 3) == 0) {
-                if constexpr (DEFER) fp4_flush_witness(wloc, wit + kWitLevels * q0, kWitLevels * nq_tile, wv, lane_e);
+                fp4_flush_witness(wloc, wit + kWitLevels * q0, kWitLevels * nq_tile, wv, lane_e);
                 // k distinct references below one of a query's witness
-                // levels make that level a bound (applied after the inserts:
-                // the candidate counts above need the bounds this tile started
-                // from)
+                // levels make that level a bound
 #pragma unroll
                 for (int h = 0; h < kQB4 / 64; ++h) {
                     const int i = lane_e + 64 * h;
@@ -1161,7 +1138,6 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
                     lthr[i] = b;
                 }
                 wave_lds_sync();
-                refresh_lbnd();
             }
         }
     }
@@ -1169,21 +1145,21 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
         wave_lds_sync();
         for (int i = lane; i < nq_tile; i += 64)
             fills[(size_t)(q0 + i) * n_workers_r + worker] = lfill[i];
-        if (DEFER && witness) fp4_flush_witness(wloc, wit + kWitLevels * q0, kWitLevels * nq_tile, wv, lane);
+        if (witness) fp4_flush_witness(wloc, wit + kWitLevels * q0, kWitLevels * nq_tile, wv, lane);
     }
 }
 
-
-template <int MODE, int EPI, bool KCHUNKS>
+template <int EPI, bool KCHUNKS, int NA>
 __global__ __launch_bounds__(kWGM) void fp4_scan_kernel(
-    const ScanParams p, const uint8_t* __restrict__ qx, int32_t kpad,
+    const ScanParams p, int mode, const uint8_t* __restrict__ qx, int32_t kpad,
     const int32_t* __restrict__ pcq, int32_t* __restrict__ out, uint64_t* __restrict__ lists,
     uint32_t* __restrict__ fills, const uint32_t* __restrict__ thr_init,
     const uint32_t* __restrict__ level, uint32_t* __restrict__ wit,
     const int32_t* __restrict__ thr, unsigned long long* __restrict__ hit_count,
     uint64_t* __restrict__ hit_keys, int32_t* __restrict__ hit_cnt)
 {
-    const int n_qtiles = (p.q_hi - p.q_lo + kQB4 - 1) / kQB4;
+    const int n_q = p.q_hi - p.q_lo;
+    const int n_qtiles = (n_q + kQB4 - 1) / kQB4;
     const int wg = xcd_local_index((int)blockIdx.x, (int)gridDim.x);
     const int qt_idx = wg % n_qtiles;
     const int wr_g = wg / n_qtiles;
@@ -1198,9 +1174,11 @@ __global__ __launch_bounds__(kWGM) void fp4_scan_kernel(
     w.qx = qx;
     w.kpad = kpad;
     w.pcq = pcq;
+    w.mode = mode;
     w.qmode = p.qmode;
-    w.q0 = p.q_lo + qt_idx * kQB4;
-    w.nq_tile = min(kQB4, p.q_hi - w.q0);
+    const int t0 = fp4_tile_begin(n_q, n_qtiles, qt_idx);
+    w.q0 = p.q_lo + t0;
+    w.nq_tile = min(fp4_tile_begin(n_q, n_qtiles, qt_idx + 1), n_q) - t0;
     w.slot = wr_g;
     w.n_slots = p.n_rsplit;
     w.k = p.k;
@@ -1218,18 +1196,13 @@ __global__ __launch_bounds__(kWGM) void fp4_scan_kernel(
     w.hit_keys = hit_keys;
     w.hit_cnt = hit_cnt;
     w.hit_cap = p.hit_cap;
-    w.multi_chunk = kpad > kKChunk4;
-    // (the full-count epilogue keeps one instance: its partial tiles are
-    // rare, and a second instance costs its loop register spills)
-    if (EPI == EPI_FULL || w.nq_tile > kQB4 - 16) fp4_work<MODE, EPI, KCHUNKS, false, true>(w);
-    else fp4_work<MODE, EPI, KCHUNKS, EPI != EPI_FULL, true>(w);
+    fp4_work<EPI, KCHUNKS, NA>(w);
 }
 
 // The staged codes of one 32-locus query word: the reciprocals of the
 // reference values, so that every product is 1; doubled for identity
-// queries (products 2: the scan then accumulates 2 D, the XOR count's
-// multiple of D).  (e2m1 codes: 0x1 = 0.5, 0x2 = 1.0, 0x4 = 2.0, 0x6 = 4.0;
-// a code times a 0/1 nibble is that code or 0.)
+// queries (products 2).  (e2m1 codes: 0x1 = 0.5, 0x2 = 1.0, 0x4 = 2.0,
+// 0x6 = 4.0; a code times a 0/1 nibble is that code or 0.)
 __device__ __forceinline__ uint4 fp4_query_codes(uint32_t w, bool dbl)
 {
     uint4 v;
@@ -1240,54 +1213,55 @@ __device__ __forceinline__ uint4 fp4_query_codes(uint32_t w, bool dbl)
     return v;
 }
 
-// Staged queries for the fp4 kernel: for every 32-locus word, 4 dwords in the
-// element order above (loci >= L cleared), plus popcount(Q_q).
-__global__ void expand_queries_fp4_kernel(const uint64_t* __restrict__ q, int32_t n_q,
-                                          int32_t row_words, int32_t n_loci, int mode,
-                                          const int32_t* __restrict__ qmode,
-                                          uint8_t* __restrict__ qx, int32_t kpad,
-                                          int32_t* __restrict__ pcq)
+// One wave stages one query row and counts its bits.  Word wi = 16 g + 4 kg + t
+// of the row goes to the place the scan's LDS copy reads: half g / 2, k quarter
+// kg, group parity, step t.
+__device__ __forceinline__ void fp4_expand_row(const uint64_t* __restrict__ q, int32_t n_loci, bool identity,
+                                               int32_t kpad, uint8_t* __restrict__ qx, int32_t* __restrict__ pcq)
 {
+    const int lane = lane_id();
     const int32_t words = kpad / 32;
-    const int64_t total = (int64_t)n_q * words;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = t / words;
-        const int32_t wi = (int32_t)(t - i * words);
-        const int32_t k0 = wi * 32;
-        uint32_t w = 0;
-        if (k0 < n_loci) {
-            w = reinterpret_cast<const uint32_t*>(q + i * row_words)[wi];
-            if (k0 + 32 > n_loci) w &= (1u << (n_loci - k0)) - 1u;
+    int32_t bits = 0;
+    for (int32_t wi = lane; wi < words; wi += 64) {
+        const int32_t left = n_loci - wi * 32;
+        uint32_t v = 0;
+        if (left > 0) {
+            v = reinterpret_cast<const uint32_t*>(q)[wi];
+            if (left < 32) v &= (1u << left) - 1u;
         }
-        const int md = mode == kModePerQuery ? qmode[i] : mode;
-        reinterpret_cast<uint4*>(qx + i * (kpad / 2))[wi] = fp4_query_codes(w, md == FID_MODE_IDENTITY);
+        bits += __popc(v);
+        const int32_t g = wi >> 4, at = (g >> 1) * 32 + ((wi >> 2) & 3) * 8 + (g & 1) * 4 + (wi & 3);
+        reinterpret_cast<uint4*>(qx)[at] = fp4_query_codes(v, identity);
     }
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_q;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        int32_t s = 0;
-        const int32_t full = n_loci >> 6;
-        for (int32_t w = 0; w < full; ++w) s += __popcll(q[i * row_words + w]);
-        if (n_loci & 63) s += __popcll(q[i * row_words + full] & ((1ull << (n_loci & 63)) - 1ull));
-        pcq[i] = s;
-    }
+    for (int o = 32; o > 0; o >>= 1) bits += __shfl_xor(bits, o);
+    if (lane == 0) *pcq = bits;
+}
+
+constexpr int kExpandWaves = 4;
+
+// Staged queries for the fp4 kernel: for every 32-locus word, 4 dwords in the
+// element order above (zero past the row), plus popcount(Q_q).
+__global__ __launch_bounds__(64 * kExpandWaves) void expand_queries_fp4_kernel(
+    const uint64_t* __restrict__ q, int32_t n_q, int32_t row_words, int32_t n_loci, int mode,
+    const int32_t* __restrict__ qmode, uint8_t* __restrict__ qx, int32_t kpad, int32_t* __restrict__ pcq)
+{
+    const int64_t i = (int64_t)blockIdx.x * kExpandWaves + (threadIdx.x >> 6);
+    if (i >= n_q) return;
+    const int md = mode == kModePerQuery ? qmode[i] : mode;
+    fp4_expand_row(q + i * row_words, n_loci, md == FID_MODE_IDENTITY, kpad, qx + i * (kpad / 2), pcq + i);
 }
 
 hipError_t launch_expand_queries_fp4(const uint64_t* q, int32_t n_q, int32_t row_words,
                                      int32_t n_loci, int mode, const int32_t* qmode, uint8_t* qx,
                                      int32_t kpad, int32_t* pcq, hipStream_t s)
 {
-    const int64_t total = (int64_t)n_q * (kpad / 32);
-    int64_t blocks = (total + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(expand_queries_fp4_kernel, dim3((unsigned)blocks), dim3(256), 0, s, q, n_q,
+    const unsigned blocks = (unsigned)((n_q + kExpandWaves - 1) / kExpandWaves);
+    hipLaunchKernelGGL(expand_queries_fp4_kernel, dim3(blocks), dim3(64 * kExpandWaves), 0, s, q, n_q,
                        row_words, n_loci, mode, qmode, qx, kpad, pcq);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------- batched passes
-static size_t fp4_lds_bytes(int32_t kpad);
 
 // Persistent fp4 pass: every workgroup takes work items from the queue of
 // its own XCD (workgroups are dealt to the 8 XCDs round-robin, so those of
@@ -1301,7 +1275,8 @@ __global__ __launch_bounds__(kWGM) void fp4_batch_kernel(const Fp4BatchSet* __re
                                                          const int32_t* __restrict__ queue_off,
                                                          unsigned int* __restrict__ counters)
 {
-    __shared__ int s_item;
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem4[];
+    int& s_item = *reinterpret_cast<int*>(smem4 + kLdsFp4);
     const int home = (int)(blockIdx.x & 7u);
     for (int h = 0; h < 8; ++h) {
         const int qi = (home + h) & 7;
@@ -1316,188 +1291,164 @@ __global__ __launch_bounds__(kWGM) void fp4_batch_kernel(const Fp4BatchSet* __re
             const int it = __builtin_amdgcn_readfirstlane(s_item);
             __syncthreads();  // every wave has read s_item before the next item overwrites it
             if (it < 0) break;
-            const Fp4BatchItem item = items[it];
-            const Fp4BatchSet& S = sets[item.set];
+            const Fp4BatchItem& I = items[it];
+            const Fp4BatchSet& S = sets[uni(I.set)];
             Fp4Work w;
-            w.db = S.db;
-            w.r_lo = S.r_lo;
-            w.r_hi = S.r_hi;
-            w.base = (S.r_lo / kDbTileRefs) * kDbTileRefs;
-            w.tb = item.tb;
-            w.te = item.te;
-            w.qx = S.qx;
-            w.kpad = S.kpad;
-            w.multi_chunk = S.kpad > kKChunk4;
-            w.pcq = S.pcq;
-            w.qmode = S.qmode;
-            w.q0 = item.qtile * kQB4;
-            w.nq_tile = min(kQB4, S.n_q - w.q0);
-            w.slot = item.slot;
-            w.n_slots = S.n_slots;
-            w.k = S.k;
-            w.out = S.out;
-            w.ld = S.ld;
+            w.db.words = uni(S.db.words);
+            w.db.pc = uni(S.db.pc);
+            w.db.n_refs = 0;
+            w.db.nblk = 0;
+            w.db.n_loci = uni(S.db.n_loci);
+            w.db.w4 = uni(S.db.w4);
+            w.r_lo = uni(S.r_lo);
+            w.r_hi = uni(S.r_hi);
+            w.base = (w.r_lo / kDbTileRefs) * kDbTileRefs;
+            w.tb = uni(I.tb);
+            w.te = uni(I.te);
+            w.qx = uni(S.qx);
+            w.kpad = uni(S.kpad);
+            w.pcq = uni(S.pcq);
+            w.mode = kModePerQuery;
+            w.qmode = uni(S.qmode);
+            const int n_q = uni(S.n_q), n_qtiles = (n_q + kQB4 - 1) / kQB4, qtile = uni(I.qtile);
+            w.q0 = fp4_tile_begin(n_q, n_qtiles, qtile);
+            w.nq_tile = min(fp4_tile_begin(n_q, n_qtiles, qtile + 1), n_q) - w.q0;
+            w.slot = uni(I.slot);
+            w.n_slots = uni(S.n_slots);
+            w.k = uni(S.k);
+            w.out = uni(S.out);
+            w.ld = uni(S.ld);
             w.out_q_base = 0;
-            w.out_r_base = S.out_r_base;
-            w.lists = S.lists;
-            w.fills = S.fills;
-            w.thr_init = S.thr_init;
-            w.level = S.level;
-            w.wit = S.wit;
+            w.out_r_base = uni(S.out_r_base);
+            w.lists = uni(S.lists);
+            w.fills = uni(S.fills);
+            w.thr_init = uni(S.thr_init);
+            w.level = uni(S.level);
+            w.wit = uni(S.wit);
             w.thr = nullptr;
             w.hit_count = nullptr;
             w.hit_keys = nullptr;
             w.hit_cnt = nullptr;
             w.hit_cap = 0;
-            // the end-of-tile drain writes its lists itself here: with two
-            // copies of the scan in the persistent kernel, the inline stores
-            // of the deferred form leave too few registers (spills inside the
-            // scan loop), and a single copy that skips empty row blocks costs
-            // full tiles 8%
-            if (EPI == EPI_FULL || w.nq_tile > kQB4 - 16) fp4_work<kModePerQuery, EPI, true, false, false>(w);
-            else fp4_work<kModePerQuery, EPI, true, EPI != EPI_FULL, false>(w);
+            switch (fp4_tile_blocks(w.nq_tile)) {
+                case 1:
+                case 2: fp4_work<EPI, true, 2>(w); break;
+                case 3:
+                case 4: fp4_work<EPI, true, 4>(w); break;
+                case 5: fp4_work<EPI, true, 5>(w); break;
+                case 6: fp4_work<EPI, true, 6>(w); break;
+                case 7: fp4_work<EPI, true, 7>(w); break;
+                default: fp4_work<EPI, true, 8>(w); break;
+            }
             __syncthreads();  // the next item restages the LDS tile
         }
     }
+}
+
+template <int EPI>
+static hipError_t launch_fp4_batch_t(const Fp4BatchSet* sets, const Fp4BatchItem* items, const int32_t* queue_off,
+                                     unsigned int* counters, int32_t grid, hipStream_t s)
+{
+    const hipError_t e = lds_opt_in<&fp4_batch_kernel<EPI>>((int)kLdsFp4 + 16);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fp4_batch_kernel<EPI>, dim3((unsigned)grid), dim3(kWGM), kLdsFp4 + 16, s, sets, items, queue_off,
+                       counters);
+    return hipGetLastError();
 }
 
 hipError_t launch_fp4_batch(int epi, const Fp4BatchSet* sets, const Fp4BatchItem* items, const int32_t* queue_off,
                             unsigned int* counters, int32_t grid, hipStream_t s)
 {
     if (grid <= 0) return hipSuccess;
-    const size_t lds = fp4_lds_bytes(kKChunk4);
-    if (epi == EPI_FULL) {
-        const hipError_t e = lds_opt_in<&fp4_batch_kernel<EPI_FULL>>((int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(fp4_batch_kernel<EPI_FULL>, dim3((unsigned)grid), dim3(kWGM), lds, s, sets, items,
-                           queue_off, counters);
-    } else if (epi == EPI_TOPK) {
-        const hipError_t e = lds_opt_in<&fp4_batch_kernel<EPI_TOPK>>((int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(fp4_batch_kernel<EPI_TOPK>, dim3((unsigned)grid), dim3(kWGM), lds, s, sets, items,
-                           queue_off, counters);
-    } else {
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    if (epi == EPI_FULL) return launch_fp4_batch_t<EPI_FULL>(sets, items, queue_off, counters, grid, s);
+    if (epi == EPI_TOPK) return launch_fp4_batch_t<EPI_TOPK>(sets, items, queue_off, counters, grid, s);
+    return hipErrorInvalidValue;
 }
 
-__global__ void expand_batch_fp4_kernel(const Fp4ExpandJob* __restrict__ jobs, int32_t n_jobs, int64_t total_words,
-                                        int64_t total_q, const int32_t* __restrict__ qmode,
-                                        int32_t* __restrict__ pcq)
+// One wave per query of any job.
+__global__ __launch_bounds__(64 * kExpandWaves) void expand_batch_fp4_kernel(const Fp4ExpandJob* __restrict__ jobs,
+                                                                             int32_t n_jobs, int64_t total_q,
+                                                                             const int32_t* __restrict__ qmode,
+                                                                             int32_t* __restrict__ pcq)
 {
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total_words;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        int a = 0, b = n_jobs;  // the last job with w_off <= t
-        while (b - a > 1) {
-            const int m = (a + b) >> 1;
-            if (jobs[m].w_off <= t) a = m;
-            else b = m;
-        }
-        const Fp4ExpandJob& J = jobs[a];
-        const int32_t words = J.kpad / 32;
-        const int64_t rel = t - J.w_off;
-        const int64_t i = rel / words;
-        const int32_t wi = (int32_t)(rel - i * words);
-        const int32_t k0 = wi * 32;
-        uint32_t w = 0;
-        if (k0 < J.n_loci) {
-            w = reinterpret_cast<const uint32_t*>(J.q + i * J.row_words)[wi];
-            if (k0 + 32 > J.n_loci) w &= (1u << (J.n_loci - k0)) - 1u;
-        }
-        reinterpret_cast<uint4*>(J.qx + i * (J.kpad / 2))[wi] =
-            fp4_query_codes(w, qmode[J.q_off + i] == FID_MODE_IDENTITY);
+    const int64_t g = (int64_t)blockIdx.x * kExpandWaves + (threadIdx.x >> 6);
+    if (g >= total_q) return;
+    int a = 0, b = n_jobs;  // the last job with q_off <= g
+    while (b - a > 1) {
+        const int m = (a + b) >> 1;
+        if (jobs[m].q_off <= g) a = m;
+        else b = m;
     }
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total_q;
-         g += (int64_t)gridDim.x * blockDim.x) {
-        int a = 0, b = n_jobs;  // the last job with q_off <= g
-        while (b - a > 1) {
-            const int m = (a + b) >> 1;
-            if (jobs[m].q_off <= g) a = m;
-            else b = m;
-        }
-        const Fp4ExpandJob& J = jobs[a];
-        const uint64_t* row = J.q + (g - J.q_off) * J.row_words;
-        int32_t c = 0;
-        const int32_t full = J.n_loci >> 6;
-        for (int32_t w = 0; w < full; ++w) c += __popcll(row[w]);
-        if (J.n_loci & 63) c += __popcll(row[full] & ((1ull << (J.n_loci & 63)) - 1ull));
-        pcq[g] = c;
-    }
+    const Fp4ExpandJob& J = jobs[a];
+    const int64_t i = g - J.q_off;
+    fp4_expand_row(J.q + i * J.row_words, J.n_loci, qmode[g] == FID_MODE_IDENTITY, J.kpad, J.qx + i * (J.kpad / 2),
+                   pcq + g);
 }
 
-hipError_t launch_expand_batch_fp4(const Fp4ExpandJob* jobs, int32_t n_jobs, int64_t total_words, int64_t total_q,
-                                   const int32_t* qmode, int32_t* pcq, hipStream_t s)
+hipError_t launch_expand_batch_fp4(const Fp4ExpandJob* jobs, int32_t n_jobs, int64_t total_q, const int32_t* qmode,
+                                   int32_t* pcq, hipStream_t s)
 {
     if (n_jobs <= 0) return hipSuccess;
-    int64_t blocks = ((total_words > total_q ? total_words : total_q) + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(expand_batch_fp4_kernel, dim3((unsigned)blocks), dim3(256), 0, s, jobs, n_jobs, total_words,
-                       total_q, qmode, pcq);
+    const unsigned blocks = (unsigned)((total_q + kExpandWaves - 1) / kExpandWaves);
+    hipLaunchKernelGGL(expand_batch_fp4_kernel, dim3(blocks), dim3(64 * kExpandWaves), 0, s, jobs, n_jobs, total_q,
+                       qmode, pcq);
     return hipGetLastError();
 }
 
-// Loci padded to whole 4-unit load groups (512 loci); zero on the query side.
-int fp4_kpad(int32_t n_loci) { return ((n_loci + 511) / 512) * 512; }
+// Loci padded to whole LDS halves (1024 loci); zero on the query side.
+int fp4_kpad(int32_t n_loci) { return ((n_loci + kHalfLoci4 - 1) / kHalfLoci4) * kHalfLoci4; }
 int fp4_max_kpad() { return kMaxKpad4; }
 int fp4_refs_per_wg() { return kRefsPerWG4; }
 int fp4_queries_per_wg() { return kQB4; }
 int fp4_list_workers_per_wg() { return kWavesM; }
 
-static size_t fp4_lds_bytes(int32_t kpad)
+template <int EPI, bool KCHUNKS, int NA>
+static hipError_t launch_fp4_t(int mode, const ScanParams& p, const MfmaBuffers& b, hipStream_t s)
 {
-    (void)kpad;
-    return (size_t)kQB4 * kRowBytes4 + 2 * (size_t)kWavesM * kQB4 * 4 + (size_t)kWavesM * 128 * 4 +
-           3 * (size_t)kQB4 * 4 + 2 * (size_t)kWitLevels * kQB4 * 4 + (size_t)kWavesM * kQB4 * 4 +
-           2 * (size_t)kWavesM * kCandQ4 * 4 + (size_t)kWitLevels * kQB4 * 4;
-}
-// (the persistent batch kernel adds one static int for its work queue)
-static_assert(kQB4 * kRowBytes4 + 2 * kWavesM * kQB4 * 4 + kWavesM * 128 * 4 + 3 * kQB4 * 4 +
-                      2 * kWitLevels * kQB4 * 4 + kWavesM * kQB4 * 4 + 2 * kWavesM * kCandQ4 * 4 +
-                      kWitLevels * kQB4 * 4 + 16 <= 163840,
-              "fp4 query tile and epilogue state must fit the 160 KiB LDS");
-static_assert(kKChunk4 % 512 == 0, "chunks hold whole 4-unit load groups");
-
-template <int MODE, int EPI, bool KCHUNKS>
-static hipError_t launch_fp4_t(const ScanParams& p, const MfmaBuffers& b, hipStream_t s)
-{
-    if (b.kpad > kMaxKpad4 || b.kpad % 512 != 0) return hipErrorInvalidValue;
     const int n_qtiles = (p.q_hi - p.q_lo + kQB4 - 1) / kQB4;
     const int64_t blocks = (int64_t)n_qtiles * p.n_rsplit;
-    const hipError_t e = lds_opt_in<&fp4_scan_kernel<MODE, EPI, KCHUNKS>>((int)fp4_lds_bytes(kKChunk4));
+    const hipError_t e = lds_opt_in<&fp4_scan_kernel<EPI, KCHUNKS, NA>>((int)kLdsFp4);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((fp4_scan_kernel<MODE, EPI, KCHUNKS>), dim3((unsigned)blocks), dim3(kWGM),
-                       fp4_lds_bytes(b.kpad), s, p, b.qx, b.kpad, b.pcq, b.out, b.lists, b.fills,
-                       b.thr_init, b.level, b.wit, b.thr, b.hit_count, b.hit_keys, b.hit_cnt);
+    hipLaunchKernelGGL((fp4_scan_kernel<EPI, KCHUNKS, NA>), dim3((unsigned)blocks), dim3(kWGM), kLdsFp4, s, p, mode,
+                       b.qx, b.kpad, b.pcq, b.out, b.lists, b.fills, b.thr_init, b.level, b.wit, b.thr, b.hit_count,
+                       b.hit_keys, b.hit_cnt);
     return hipGetLastError();
+}
+
+// The instance for the largest of the launch's (even) query tiles.
+template <int EPI, bool KCHUNKS>
+static hipError_t launch_fp4_na(int mode, const ScanParams& p, const MfmaBuffers& b, hipStream_t s)
+{
+    const int blocks = fp4_tile_blocks(p.q_hi - p.q_lo), n_qtiles = (p.q_hi - p.q_lo + kQB4 - 1) / kQB4;
+    switch ((blocks + n_qtiles - 1) / n_qtiles) {
+        case 1:
+        case 2: return launch_fp4_t<EPI, KCHUNKS, 2>(mode, p, b, s);
+        case 3:
+        case 4: return launch_fp4_t<EPI, KCHUNKS, 4>(mode, p, b, s);
+        case 5: return launch_fp4_t<EPI, KCHUNKS, 5>(mode, p, b, s);
+        case 6: return launch_fp4_t<EPI, KCHUNKS, 6>(mode, p, b, s);
+        case 7: return launch_fp4_t<EPI, KCHUNKS, 7>(mode, p, b, s);
+        default: return launch_fp4_t<EPI, KCHUNKS, 8>(mode, p, b, s);
+    }
 }
 
 template <bool KCHUNKS>
 static hipError_t launch_fp4_k(int mode, int epi, const ScanParams& p, const MfmaBuffers& b, hipStream_t s)
 {
-    if (mode == kModePerQuery) {
-        if (epi == EPI_FULL) return launch_fp4_t<kModePerQuery, EPI_FULL, KCHUNKS>(p, b, s);
-        if (epi == EPI_TOPK) return launch_fp4_t<kModePerQuery, EPI_TOPK, KCHUNKS>(p, b, s);
-        return hipErrorInvalidValue;
+    switch (epi) {
+        case EPI_FULL: return launch_fp4_na<EPI_FULL, KCHUNKS>(mode, p, b, s);
+        case EPI_TOPK: return launch_fp4_na<EPI_TOPK, KCHUNKS>(mode, p, b, s);
+        case EPI_BOTH: return launch_fp4_na<EPI_BOTH, KCHUNKS>(mode, p, b, s);
+        default: return launch_fp4_na<EPI_THRESH, KCHUNKS>(mode, p, b, s);
     }
-    if (mode == FID_MODE_MIXTURE) {
-        if (epi == EPI_FULL) return launch_fp4_t<FID_MODE_MIXTURE, EPI_FULL, KCHUNKS>(p, b, s);
-        if (epi == EPI_TOPK) return launch_fp4_t<FID_MODE_MIXTURE, EPI_TOPK, KCHUNKS>(p, b, s);
-        if (epi == EPI_BOTH) return launch_fp4_t<FID_MODE_MIXTURE, EPI_BOTH, KCHUNKS>(p, b, s);
-        return launch_fp4_t<FID_MODE_MIXTURE, EPI_THRESH, KCHUNKS>(p, b, s);
-    }
-    if (epi == EPI_FULL) return launch_fp4_t<FID_MODE_IDENTITY, EPI_FULL, KCHUNKS>(p, b, s);
-    if (epi == EPI_TOPK) return launch_fp4_t<FID_MODE_IDENTITY, EPI_TOPK, KCHUNKS>(p, b, s);
-    if (epi == EPI_BOTH) return launch_fp4_t<FID_MODE_IDENTITY, EPI_BOTH, KCHUNKS>(p, b, s);
-    return launch_fp4_t<FID_MODE_IDENTITY, EPI_THRESH, KCHUNKS>(p, b, s);
 }
 
 hipError_t launch_fp4_scan(int mode, int epi, const ScanParams& p, const MfmaBuffers& b,
                            hipStream_t s)
 {
     if (p.n_rsplit <= 0) return hipSuccess;
-    if (b.kpad > kKChunk4) return launch_fp4_k<true>(mode, epi, p, b, s);
+    if (b.kpad > kMaxKpad4 || b.kpad != fp4_kpad(p.db.n_loci)) return hipErrorInvalidValue;
+    if (b.kpad > 2 * kHalfLoci4) return launch_fp4_k<true>(mode, epi, p, b, s);
     return launch_fp4_k<false>(mode, epi, p, b, s);
 }
 
