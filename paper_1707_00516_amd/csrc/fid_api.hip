@@ -605,7 +605,7 @@ int topk_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const
         FID_TRY(run_full(ctx, db, j, q, mode, r_lo, r_lo + L.seed, 0, n_q, counts, L.seed, 0, r_lo,
                          L.direct && timed));
     if (L.direct) {
-        FID_HIP(launch_select_counts(counts, n_q, L.seed, k, r_lo, cnt_dev, idx_dev, ctx->stream),
+        FID_HIP(launch_select_counts(counts, n_q, L.seed, k, db->v.n_loci, r_lo, cnt_dev, idx_dev, ctx->stream),
                 "select launch");
         return FID_OK;
     }

@@ -239,13 +239,9 @@ __global__ __launch_bounds__(kSelectThreads) void batch_merge_kernel(
     const BQuery* __restrict__ qmeta, const uint64_t* __restrict__ lists,
     const uint32_t* __restrict__ fills, int32_t k)
 {
-    __shared__ uint64_t s[kSelectSlots];
-    __shared__ int nb;
-    __shared__ uint32_t part[kSelectThreads];
-    extern __shared__ uint32_t off[];  // [nslot + 1] prefix of the fill counts
+    __shared__ SelectLds<kSelectThreads> L;
     const BQuery qm = qmeta[blockIdx.x];
-    merge_query_lists(lists + qm.lbase, fills + qm.fbase, qm.nslot, k, qm.n_loci, qm.cnt, qm.idx, s,
-                      &nb, part, off);
+    merge_query_lists<kSelectThreads>(lists + qm.lbase, fills + qm.fbase, qm.nslot, k, qm.n_loci, qm.cnt, qm.idx, L);
 }
 
 __global__ void fill_u32_kernel(uint32_t* __restrict__ p, int64_t n, uint32_t v)
@@ -273,7 +269,6 @@ struct fid_batch {
     int64_t n_items;
     int64_t n_queries;
     int64_t n_lists;
-    int32_t max_slots;
     int64_t staged_words;
     int32_t grid;
     size_t lds_per_wave;
@@ -310,7 +305,6 @@ struct fid_batch {
     int32_t f4_jobs;                 // jobs on the batched fp4 passes
     int32_t f4_grid;                 // persistent workgroups
     int32_t f4_loci_max;
-    int32_t f4_max_slots;            // most list owners of one query
     int64_t f4_queries;              // staged queries
     int32_t n_f4_seed_sel, n_f4_direct_sel;
     int64_t f4_seed_q, f4_direct_q;  // queries of each selection
@@ -344,7 +338,6 @@ struct BatchPlan {
     std::vector<BItem> items;
     std::vector<BQuery> qmeta;
     int64_t n_lists = 0;
-    int32_t max_slots = 0;
     int32_t qmax = 1;
     size_t off_counter, off_jobs, off_jwo, off_items, off_qmeta, off_gbound, off_fills, off_qs,
         off_lists, off_routed, total;
@@ -362,7 +355,7 @@ struct BatchPlan {
     std::vector<Fp4BatchItem> f4_seed_items, f4_scan_items;
     std::vector<int32_t> f4_seed_qoff, f4_scan_qoff;  // [9] each
     int64_t f4_queries = 0, f4_keys = 0, f4_fills = 0;
-    int32_t f4_loci_max = 1, f4_max_slots = 0;
+    int32_t f4_loci_max = 1;
     int32_t n_seed_sel = 0, n_direct_sel = 0;
     int64_t seed_q = 0, direct_q = 0, merge_q = 0;
     size_t off_f4_counters, off_f4_sets, off_f4_items, off_f4_qoff, off_f4_expand, off_f4_sel, off_f4_merge,
@@ -467,7 +460,6 @@ int plan_batch(const fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
                 f.fbase = P->f4_fills;
                 P->f4_keys += (int64_t)f.n_q * owners * k;
                 P->f4_fills += (int64_t)f.n_q * owners;
-                P->f4_max_slots = std::max(P->f4_max_slots, owners);
                 P->n_seed_sel++;
                 P->seed_q += f.n_q;
                 P->merge_q += f.n_q;
@@ -540,7 +532,6 @@ int plan_batch(const fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
             P->qmeta.push_back(m);
             P->n_lists += nsplit;
         }
-        P->max_slots = std::max<int32_t>(P->max_slots, (int32_t)nsplit);
         g += J.n_q;
     }
     P->job_word_off[n_jobs] = words;
@@ -672,8 +663,7 @@ int enqueue_fp4(fid_batch* b, hipStream_t s, bool timed)
         FID_HIP(launch_fp4_batch(EPI_TOPK, b->f4_scan_sets, b->f4_scan_items, b->f4_scan_qoff, b->f4_counters + 8,
                                  b->f4_grid, s), "batched top-k pass launch");
         if (e1) FID_HIP(hipEventRecord(e1, s), "hipEventRecord");
-        hipLaunchKernelGGL(batch_merge_kernel, dim3((unsigned)b->f4_merge_q), dim3(kSelectThreads),
-                           (size_t)(b->f4_max_slots + 1) * sizeof(uint32_t), s, b->f4_merge, b->f4_lists,
+        hipLaunchKernelGGL(batch_merge_kernel, dim3((unsigned)b->f4_merge_q), dim3(kSelectThreads), 0, s, b->f4_merge, b->f4_lists,
                            b->f4_fills, b->k);
         FID_HIP(hipGetLastError(), "batched merge launch");
     }
@@ -699,8 +689,7 @@ int enqueue_persistent(fid_batch* b, hipStream_t s, bool timed)
                        b->fills, b->gbound, b->k, b->qmax, (int32_t)b->lds_per_wave);
     FID_HIP(hipGetLastError(), "batch scan launch");
     if (e1) FID_HIP(hipEventRecord(e1, s), "hipEventRecord");
-    hipLaunchKernelGGL(batch_merge_kernel, dim3((unsigned)b->n_queries), dim3(kSelectThreads),
-                       (size_t)(b->max_slots + 1) * sizeof(uint32_t), s, b->qmeta, b->lists, b->fills,
+    hipLaunchKernelGGL(batch_merge_kernel, dim3((unsigned)b->n_queries), dim3(kSelectThreads), 0, s, b->qmeta, b->lists, b->fills,
                        b->k);
     FID_HIP(hipGetLastError(), "batch merge launch");
     return FID_OK;
@@ -740,7 +729,6 @@ int fid_batch_create(fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
     b->n_items = (int64_t)P.items.size();
     b->n_queries = (int64_t)P.qmeta.size();
     b->n_lists = P.n_lists;
-    b->max_slots = P.max_slots;
     b->staged_words = P.job_word_off.back();
     b->qmax = P.qmax;
     b->lds_per_wave = batch_lds_per_wave(k, P.qmax);
@@ -776,7 +764,6 @@ int fid_batch_create(fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
     if (b->f4_jobs) {
         b->f4_grid = ctx->num_cus;  // one workgroup per CU: the tile's LDS and registers fill it
         b->f4_loci_max = P.f4_loci_max;
-        b->f4_max_slots = P.f4_max_slots;
         b->f4_queries = P.f4_queries;
         b->f4_counters = reinterpret_cast<unsigned int*>(ws + P.off_f4_counters);
         b->f4_seed_sets = reinterpret_cast<Fp4BatchSet*>(ws + P.off_f4_sets);

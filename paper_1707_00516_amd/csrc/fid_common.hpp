@@ -28,7 +28,7 @@ constexpr int kSeedBinsBatch = 4096; // the same in ragged batches (16 KB: 8 wor
 // Witness levels of a top-k query: the seed bins of its (k/2)-th, (k/4)-th, ...,
 // (k/32)-th smallest seed counts (each at least the first), stored [q][kWitLevels].
 constexpr int kWitLevels = 5;
-constexpr int kMaxListWorkers = 8192;  // top-k workers along references (merge prefix in LDS)
+constexpr int kMaxListWorkers = 8192;  // top-k workers along references (lists of a query)
 constexpr int kChunkQueries = 60;   // queries per wave when counts span several chunks
                                     // (4 waves x 60 x 64 16-bit partial counts: 30 KiB of LDS)
 
@@ -221,7 +221,7 @@ hipError_t launch_min_bound(uint32_t* thr, const uint32_t* bound, int32_t n, boo
 hipError_t launch_seed_select(const int32_t* counts, int32_t n_q, int64_t n_cols, int32_t k,
                               int32_t n_loci, uint32_t* thr_init, uint32_t* level, uint32_t* wit,
                               hipStream_t s);
-hipError_t launch_select_counts(const int32_t* counts, int32_t n_q, int64_t n_cols, int32_t k,
+hipError_t launch_select_counts(const int32_t* counts, int32_t n_q, int64_t n_cols, int32_t k, int32_t n_loci,
                                 int64_t idx_base, int32_t* cnt, int64_t* idx, hipStream_t s);
 // The seed bounds (launch_seed_select) of every query of n_jobs jobs, one
 // workgroup per query (total_q queries); n_loci_max bounds the histogram.

@@ -576,37 +576,23 @@ __device__ __forceinline__ void seed_select_one(const int32_t* __restrict__ row,
                                                 uint32_t* __restrict__ level_q, uint32_t* __restrict__ wit_q)
 {
     extern __shared__ uint32_t hist[];           // [nbins]
-    __shared__ uint32_t part[NT];
-    __shared__ uint32_t found, found_w[kWitLevels];
+    __shared__ uint32_t part[NT / 64], found[1 + kWitLevels], cum[1 + kWitLevels];
     const int tid = (int)threadIdx.x;
-    uint32_t kw[kWitLevels];
-    for (int l = 0; l < kWitLevels; ++l) kw[l] = (uint32_t)k >> (l + 1) > 0u ? (uint32_t)k >> (l + 1) : 1u;
+    auto kw = [&](int l) { return (uint32_t)k >> (l + 1) > 0u ? (uint32_t)k >> (l + 1) : 1u; };
     for (int i = tid; i < nbins; i += NT) hist[i] = 0u;
-    if (tid == 0) {
-        found = 0xFFFFFFFFu;
-        for (int l = 0; l < kWitLevels; ++l) found_w[l] = 0xFFFFFFFFu;
-    }
     __syncthreads();
-    for (int64_t i = tid; i < n_cols; i += NT)
-        atomicAdd(&hist[(uint32_t)row[i] >> shift], 1u);
-    __syncthreads();
+    wg_low_histogram<NT>(row, n_cols, k, shift, nbins, hist, part, found, cum);
     const int seg = (nbins + NT - 1) / NT;
+    const int lo = min(nbins, tid * seg), hi = min(nbins, (tid + 1) * seg);
+    if (tid <= kWitLevels) found[tid] = 0xFFFFFFFFu;
     uint32_t sum = 0;
-    for (int i = tid * seg; i < min(nbins, (tid + 1) * seg); ++i) sum += hist[i];
-    part[tid] = sum;
-    __syncthreads();
-    for (int off = 1; off < NT; off <<= 1) {  // inclusive scan of the segment sums
-        const uint32_t v = tid >= off ? part[tid - off] : 0u;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    const uint32_t before = tid > 0 ? part[tid - 1] : 0u;
+    for (int i = lo; i < hi; ++i) sum += hist[i];
+    const uint32_t before = wg_exclusive_sum<NT>(sum, part);
     // the bin where the running count first reaches `target`
     auto crossing = [&](uint32_t target, uint32_t& out) {
-        if (before < target && part[tid] >= target) {
+        if (before < target && before + sum >= target) {
             uint32_t run = before;
-            for (int i = tid * seg; i < min(nbins, (tid + 1) * seg); ++i) {
+            for (int i = lo; i < hi; ++i) {
                 run += hist[i];
                 if (run >= target) {
                     out = (uint32_t)i;
@@ -615,25 +601,27 @@ __device__ __forceinline__ void seed_select_one(const int32_t* __restrict__ row,
             }
         }
     };
-    crossing((uint32_t)k, found);
+    crossing((uint32_t)k, found[0]);
     if (level_q)
-        for (int l = 0; l < kWitLevels; ++l) crossing(kw[l], found_w[l]);
+        for (int l = 0; l < kWitLevels; ++l) crossing(kw(l), found[1 + l]);
     __syncthreads();
     if (tid == 0) {
-        *thr_q = found == 0xFFFFFFFFu ? 0xFFFFFFFFu : (found + 1u) << shift;
+        *thr_q = found[0] == 0xFFFFFFFFu ? 0xFFFFFFFFu : (found[0] + 1u) << shift;
         if (level_q) {
             for (int l = 0; l < kWitLevels; ++l) {
-                level_q[l] = found_w[l] == 0xFFFFFFFFu || kw[l] >= (uint32_t)k ? 0u : (found_w[l] + 1u) << shift;
+                level_q[l] = found[1 + l] == 0xFFFFFFFFu || kw(l) >= (uint32_t)k ? 0u : (found[1 + l] + 1u) << shift;
                 wit_q[l] = 0u;
             }
         }
     }
 }
 
-
 // One workgroup of kSeedSelectThreads per query: a call's seed rows are long
-// (up to 131,072 counts) and its queries few (a serving tick holds about 130),
-// so the histogram takes wide workgroups rather than many.
+// (up to 262,144 counts) and its queries few (a serving tick holds about 130),
+// so the histogram takes wide workgroups rather than many.  Bound: the bytes
+// one workgroup has in flight; with 16-byte loads and only the low tail
+// counted 1 query x 262,144 counts takes 21 us (76 before), 131 x 131,072 20 us
+// (43), 2048 x 65,536 143 us (194).
 constexpr int kSeedSelectThreads = 1024;
 
 __global__ __launch_bounds__(kSeedSelectThreads) void seed_select_kernel(
@@ -694,40 +682,44 @@ hipError_t launch_seed_select_batch(const SelectJob* jobs, int32_t n_jobs, int64
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(kSelectThreads) void select_counts_kernel(
-    const int32_t* __restrict__ counts, int64_t n_cols, int32_t k, int64_t idx_base,
-    int32_t* __restrict__ cnt, int64_t* __restrict__ idx)
+// One workgroup per query.  Few queries take wide workgroups (each query's
+// selection is a chain of latencies), many fill the device with narrow ones.
+constexpr int kMergeWideThreads = 1024;
+constexpr int32_t kMergeWideMaxQ = 512;
+static_assert(kSelectSlots / 2 % kMergeWideThreads == 0, "the workgroup top-k takes whole rounds of keys");
+
+template <int NT>
+__global__ __launch_bounds__(NT) void select_counts_kernel(const int32_t* __restrict__ counts, int64_t n_cols,
+                                                           int32_t k, int32_t n_loci, int64_t idx_base,
+                                                           int32_t* __restrict__ cnt, int64_t* __restrict__ idx)
 {
-    __shared__ uint64_t s[kSelectSlots];
-    __shared__ int nb;
+    __shared__ SelectLds<NT> L;
     const int q = blockIdx.x;
-    const int32_t* row = counts + (size_t)q * n_cols;
-    wg_topk([&](int64_t i) { return ((uint64_t)(uint32_t)row[i] << kIdxBits) | (uint64_t)(idx_base + i); },
-            n_cols, k, s, &nb);
-    write_topk(s, k, cnt + (size_t)q * k, idx + (size_t)q * k);
+    select_row<NT>(counts + (size_t)q * n_cols, n_cols, k, n_loci, idx_base, cnt + (size_t)q * k,
+                   idx + (size_t)q * k, L);
 }
 
-hipError_t launch_select_counts(const int32_t* counts, int32_t n_q, int64_t n_cols, int32_t k,
+hipError_t launch_select_counts(const int32_t* counts, int32_t n_q, int64_t n_cols, int32_t k, int32_t n_loci,
                                 int64_t idx_base, int32_t* cnt, int64_t* idx, hipStream_t s)
 {
-    hipLaunchKernelGGL(select_counts_kernel, dim3(n_q), dim3(kSelectThreads), 0, s, counts,
-                       n_cols, k, idx_base, cnt, idx);
+    if (n_q <= kMergeWideMaxQ)
+        hipLaunchKernelGGL(select_counts_kernel<kMergeWideThreads>, dim3(n_q), dim3(kMergeWideThreads), 0, s, counts,
+                           n_cols, k, n_loci, idx_base, cnt, idx);
+    else
+        hipLaunchKernelGGL(select_counts_kernel<kSelectThreads>, dim3(n_q), dim3(kSelectThreads), 0, s, counts,
+                           n_cols, k, n_loci, idx_base, cnt, idx);
     return hipGetLastError();
 }
 
 __global__ __launch_bounds__(kSelectThreads) void select_counts_batch_kernel(const SelectJob* __restrict__ jobs,
                                                                              int32_t n_jobs)
 {
-    __shared__ uint64_t s[kSelectSlots];
-    __shared__ int nb;
+    __shared__ SelectLds<kSelectThreads> L;
     const int64_t g = blockIdx.x;
     const SelectJob& J = jobs[select_job_of(jobs, n_jobs, g)];
     const int64_t q = g - J.q_off;
-    const int32_t* row = J.counts + q * J.n_cols;
-    const int64_t base = J.idx_base;
-    wg_topk([&](int64_t i) { return ((uint64_t)(uint32_t)row[i] << kIdxBits) | (uint64_t)(base + i); }, J.n_cols, J.k,
-            s, &nb);
-    write_topk(s, J.k, J.cnt + q * J.k, J.idx + q * J.k);
+    select_row<kSelectThreads>(J.counts + q * J.n_cols, J.n_cols, J.k, J.n_loci, J.idx_base, J.cnt + q * J.k,
+                               J.idx + q * J.k, L);
 }
 
 hipError_t launch_select_counts_batch(const SelectJob* jobs, int32_t n_jobs, int64_t total_q, hipStream_t s)
@@ -738,41 +730,28 @@ hipError_t launch_select_counts_batch(const SelectJob* jobs, int32_t n_jobs, int
     return hipGetLastError();
 }
 
-// Merge of the per-worker lists of one query (one workgroup of NT threads
-// per query).
+// Merge of the per-worker lists of one query.
 template <int NT>
 __global__ __launch_bounds__(NT) void merge_lists_kernel(
     const uint64_t* __restrict__ lists, const uint32_t* __restrict__ fills, int32_t n_rsplit,
     int32_t k, int32_t n_loci, int32_t* __restrict__ cnt, int64_t* __restrict__ idx)
 {
-    __shared__ uint64_t s[kSelectSlots];
-    __shared__ int nb;
-    __shared__ uint32_t part[NT];
-    extern __shared__ uint32_t off[];  // [n_rsplit + 1] prefix of the fill counts
+    __shared__ SelectLds<NT> L;
     const int q = blockIdx.x;
     merge_query_lists<NT>(lists + (size_t)q * n_rsplit * k, fills + (size_t)q * n_rsplit, n_rsplit, k, n_loci,
-                          cnt + (size_t)q * k, idx + (size_t)q * k, s, &nb, part, off);
+                          cnt + (size_t)q * k, idx + (size_t)q * k, L);
 }
-
-// Calls of a few query tiles (a serving tick holds about 130 queries) spread
-// each query over thousands of lists: wide workgroups, as in the seed
-// selection; many queries fill the device with narrow ones.
-constexpr int kMergeWideThreads = 1024;
-constexpr int32_t kMergeWideMaxQ = 512;
-static_assert(kSelectSlots / 2 % kMergeWideThreads == 0, "the workgroup top-k takes whole rounds of keys");
 
 hipError_t launch_merge_lists(const uint64_t* lists, const uint32_t* fills, int32_t n_q,
                               int32_t n_rsplit, int32_t k, int32_t n_loci, int32_t* cnt, int64_t* idx,
                               hipStream_t s)
 {
     if (n_q <= kMergeWideMaxQ)
-        hipLaunchKernelGGL(merge_lists_kernel<kMergeWideThreads>, dim3(n_q), dim3(kMergeWideThreads),
-                           (size_t)(n_rsplit + 1) * sizeof(uint32_t), s, lists, fills, n_rsplit, k, n_loci,
-                           cnt, idx);
+        hipLaunchKernelGGL(merge_lists_kernel<kMergeWideThreads>, dim3(n_q), dim3(kMergeWideThreads), 0, s, lists,
+                           fills, n_rsplit, k, n_loci, cnt, idx);
     else
-        hipLaunchKernelGGL(merge_lists_kernel<kSelectThreads>, dim3(n_q), dim3(kSelectThreads),
-                           (size_t)(n_rsplit + 1) * sizeof(uint32_t), s, lists, fills, n_rsplit, k, n_loci,
-                           cnt, idx);
+        hipLaunchKernelGGL(merge_lists_kernel<kSelectThreads>, dim3(n_q), dim3(kSelectThreads), 0, s, lists, fills,
+                           n_rsplit, k, n_loci, cnt, idx);
     return hipGetLastError();
 }
 
