@@ -101,7 +101,6 @@ namespace {
 
 constexpr int64_t kMaxRefs = (1ll << kIdxBits) - 1;
 constexpr int32_t kMaxQueries = 1 << 24;
-constexpr size_t kStatusBytes = 256;
 
 int64_t row_words_of(int32_t n_loci)
 {
@@ -121,10 +120,10 @@ size_t db_words_bytes(int64_t nblk, int64_t row_words)
     return align256((size_t)nblk * 64 * (size_t)row_words * 8 + 4 * 64 * 16);
 }
 
-// Library scratch: [status words | staged or expanded queries].  Grown on demand.
+// Library scratch: staged or expanded queries.  Grown on demand.
 int ensure_scratch(fid_ctx* ctx, size_t need)
 {
-    need = align256(need + kStatusBytes);
+    need = align256(need);
     if (need <= ctx->scratch_bytes) return FID_OK;
     if (ctx->scratch) {
         FID_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
@@ -142,9 +141,7 @@ int ensure_scratch(fid_ctx* ctx, size_t need)
     return FID_OK;
 }
 
-int* status_words(fid_ctx* ctx) { return static_cast<int*>(ctx->scratch); }
-
-char* query_area(fid_ctx* ctx) { return static_cast<char*>(ctx->scratch) + kStatusBytes; }
+char* query_area(fid_ctx* ctx) { return static_cast<char*>(ctx->scratch); }
 
 // ---------------------------------------------------------------- planning
 // Register-resident chunk width (32-bit words per lane) of the popcount scan.
@@ -365,11 +362,12 @@ struct Prepared {
 
 // Staged queries go to the context's scratch (grown on demand), or to
 // `area` when the caller provides one (query_scratch_bytes() bytes), which
-// allocates nothing.
+// allocates nothing.  clear: a hit counter to set to 0 before the scan.
 int prepare_queries(fid_ctx* ctx, const fid_db* db, const Job& j, const uint64_t* q_dev,
                     int32_t n_q, int mode, Prepared* out, const int32_t* qmode = nullptr,
-                    char* area = nullptr)
+                    char* area = nullptr, unsigned long long* clear = nullptr)
 {
+    uint64_t* const zero = reinterpret_cast<uint64_t*>(clear);
     *out = Prepared{};
     out->qmode = qmode;
     auto reserve = [&](size_t bytes) -> int { return area ? FID_OK : ensure_scratch(ctx, bytes); };
@@ -380,7 +378,7 @@ int prepare_queries(fid_ctx* ctx, const fid_db* db, const Job& j, const uint64_t
         uint8_t* qx = reinterpret_cast<uint8_t*>(qbase());
         int32_t* pcq = reinterpret_cast<int32_t*>(qbase() + xbytes);
         FID_HIP(launch_expand_queries_fp4(q_dev, n_q, db->row_words, db->v.n_loci, mode, qmode, qx, j.kpad,
-                                          pcq, ctx->stream),
+                                          pcq, ctx->stream, zero),
                 "expand_queries launch");
         out->qx = qx;
         out->pcq = pcq;
@@ -395,6 +393,7 @@ int prepare_queries(fid_ctx* ctx, const fid_db* db, const Job& j, const uint64_t
         FID_HIP(launch_expand_queries(q_dev, n_q, db->row_words, db->v.n_loci, qx, j.kpad, pcq,
                                       ctx->stream),
                 "expand_queries launch");
+        if (zero) FID_HIP(launch_fill_u64(zero, 1, 0ull, ctx->stream), "fill launch");
         out->qx = qx;
         out->pcq = pcq;
         out->qmode = qmode;
@@ -403,7 +402,7 @@ int prepare_queries(fid_ctx* ctx, const fid_db* db, const Job& j, const uint64_t
     FID_TRY(reserve((size_t)n_q * j.sh.qw * sizeof(uint32_t)));
     uint32_t* qs = reinterpret_cast<uint32_t*>(qbase());
     FID_HIP(launch_stage_queries(q_dev, n_q, db->row_words, db->v.n_loci, mode, qmode, qs, j.sh.qw,
-                                 ctx->stream),
+                                 ctx->stream, zero),
             "stage_queries launch");
     out->qs = qs;
     out->qmode = qmode;
@@ -545,6 +544,28 @@ TopkLayout topk_layout(const fid_ctx* ctx, const Job& j, int64_t r_lo, int64_t r
     return L;
 }
 
+// The scan's hits (keys, vals; their number at `counter`) to CSR.  Waits for the
+// scan, as the caller wants the total: a small total has been put in order by
+// then, a larger one is sorted after it.
+int finish_hits(fid_ctx* ctx, const unsigned long long* counter, uint64_t* keys, int32_t* vals, uint64_t* keys2,
+                int32_t* vals2, int64_t cap, int32_t n_q, int64_t* offs, int64_t* idx, int32_t* cnt,
+                int64_t* total_host)
+{
+    FID_HIP(launch_small_hits(keys, vals, counter, cap, n_q, offs, idx, cnt, ctx->host_word, ctx->stream),
+            "hits launch");
+    FID_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
+    const unsigned long long total = *ctx->host_word;
+    *total_host = (int64_t)total;
+    if ((int64_t)total > cap)
+        return fail(FID_EOVERFLOW, "%llu threshold hits exceed capacity %lld", total, (long long)cap);
+    if ((int64_t)total <= small_hits_max(n_q)) return FID_OK;
+    uint64_t* sk;
+    int32_t* sv;
+    FID_HIP(launch_sort_hits(keys, vals, keys2, vals2, (int64_t)total, &sk, &sv, ctx->stream), "sort launch");
+    FID_HIP(launch_hits_to_csr(sk, sv, (int64_t)total, n_q, offs, idx, cnt, ctx->stream), "csr launch");
+    return FID_OK;
+}
+
 int check_range(const fid_db* db, int64_t r_lo, int64_t r_hi)
 {
     if (r_lo < 0 || r_hi <= r_lo || r_hi > db->v.n_refs)
@@ -561,13 +582,12 @@ int check_modes_dev(fid_ctx* ctx, const int32_t* modes_dev, int32_t n_q)
     if (!modes_dev) return fail(FID_EINVAL, "modes pointer is NULL");
     if ((reinterpret_cast<uintptr_t>(modes_dev) & 3u) != 0) return fail(FID_EINVAL, "modes pointer not 4-byte aligned");
     FID_TRY(set_device(ctx));
-    int* bad = status_words(ctx);
-    FID_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(bad), 1, 0ull, ctx->stream), "fill launch");
+    // (nothing in flight refers to the word: every call that uses it waits)
+    *ctx->host_word = 0ull;
+    int* bad = reinterpret_cast<int*>(ctx->host_word);
     FID_HIP(launch_check_modes(modes_dev, n_q, bad, ctx->stream), "mode check launch");
-    int bad_host = 0;
-    FID_HIP(hipMemcpyAsync(&bad_host, bad, sizeof(int), hipMemcpyDeviceToHost, ctx->stream), "hipMemcpyAsync");
     FID_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-    if (bad_host)
+    if (*ctx->host_word)
         return fail(FID_EINVAL, "modes_dev holds a value other than FID_MODE_MIXTURE (0) or FID_MODE_IDENTITY (1)");
     return FID_OK;
 }
@@ -748,9 +768,14 @@ int fid_ctx_create(fid_ctx** out, int device, void* stream)
     c->timing = false;
     c->events_used = 0;
     c->fixed_scratch = nullptr;
+    c->host_word = nullptr;
     int st = fixed_scratch_address(device, &c->fixed_scratch);
-    if (!st) st = ensure_scratch(c, 0);
+    if (!st) {
+        e = hipHostMalloc(reinterpret_cast<void**>(&c->host_word), 64, hipHostMallocDefault);
+        if (e != hipSuccess) st = fail(FID_ENOMEM, "pinned allocation failed: %s", hipGetErrorString(e));
+    }
     if (st) {
+        if (c->host_word) (void)hipHostFree(c->host_word);
         delete c;
         return st;
     }
@@ -765,6 +790,7 @@ int fid_ctx_destroy(fid_ctx* ctx)
     if (!st) {
         hipStreamSynchronize(ctx->stream);
         if (ctx->scratch) hipFree(ctx->scratch);
+        if (ctx->host_word) hipHostFree(ctx->host_word);
         for (auto& ev : ctx->events) {
             hipEventDestroy(ev.first);
             hipEventDestroy(ev.second);
@@ -845,14 +871,13 @@ int fid_pack(fid_ctx* ctx, const uint8_t* bytes_dev, int64_t n_rows, int32_t n_l
     if (ld_bytes < n_loci) return fail(FID_EINVAL, "ld_bytes < n_loci");
     if (!aligned16(rows_dev)) return fail(FID_EINVAL, "rows_dev not 16-byte aligned");
     FID_TRY(set_device(ctx));
-    int* bad = status_words(ctx);
-    FID_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(bad), 1, 0ull, ctx->stream), "fill launch");
+    // (nothing in flight refers to the word: every call that uses it waits)
+    *ctx->host_word = 0ull;
+    int* bad = reinterpret_cast<int*>(ctx->host_word);
     FID_HIP(launch_pack(bytes_dev, n_rows, n_loci, ld_bytes, (int32_t)rw, rows_dev, bad, ctx->stream),
             "pack launch");
-    int bad_host = 0;
-    FID_HIP(hipMemcpyAsync(&bad_host, bad, sizeof(int), hipMemcpyDeviceToHost, ctx->stream), "hipMemcpyAsync");
     FID_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-    if (bad_host) return fail(FID_EINVAL, "profile bytes must be 0 or 1");
+    if (*ctx->host_word) return fail(FID_EINVAL, "profile bytes must be 0 or 1");
     return FID_OK;
 }
 
@@ -895,14 +920,13 @@ int fid_pack_genotypes(fid_ctx* ctx, const uint8_t* geno_dev, int64_t n_rows, in
     if (ld_bytes < n_loci) return fail(FID_EINVAL, "ld_bytes < n_loci");
     if (!aligned16(rows_dev)) return fail(FID_EINVAL, "rows_dev not 16-byte aligned");
     FID_TRY(set_device(ctx));
-    int* bad = status_words(ctx);
-    FID_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(bad), 1, 0ull, ctx->stream), "fill launch");
+    // (nothing in flight refers to the word: every call that uses it waits)
+    *ctx->host_word = 0ull;
+    int* bad = reinterpret_cast<int*>(ctx->host_word);
     FID_HIP(launch_pack_genotypes(geno_dev, n_rows, n_loci, ld_bytes, (int32_t)rw, rows_dev, bad, ctx->stream),
             "genotype pack launch");
-    int bad_host = 0;
-    FID_HIP(hipMemcpyAsync(&bad_host, bad, sizeof(int), hipMemcpyDeviceToHost, ctx->stream), "hipMemcpyAsync");
     FID_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-    if (bad_host) return fail(FID_EINVAL, "genotypes must be 0, 1 or 2");
+    if (*ctx->host_word) return fail(FID_EINVAL, "genotypes must be 0, 1 or 2");
     return FID_OK;
 }
 
@@ -1399,8 +1423,6 @@ int fid_compare_threshold(fid_ctx* ctx, const fid_db* db, const uint64_t* q_dev,
     if (ws_bytes < need) return fail(FID_ENOMEM, "workspace %zu bytes < required %zu", ws_bytes, need);
     FID_TRY(set_device(ctx));
     const Job j = make_job(ctx, db, n_q);
-    Prepared q;
-    FID_TRY(prepare_queries(ctx, db, j, q_dev, n_q, mode, &q));
     const size_t c = (size_t)(cap > 0 ? cap : 1);
     char* ws = static_cast<char*>(ws_dev);
     unsigned long long* counter = reinterpret_cast<unsigned long long*>(ws);
@@ -1408,7 +1430,8 @@ int fid_compare_threshold(fid_ctx* ctx, const fid_db* db, const uint64_t* q_dev,
     uint64_t* keys2 = reinterpret_cast<uint64_t*>(ws + 256 + align256(c * 8));
     int32_t* vals = reinterpret_cast<int32_t*>(ws + 256 + 2 * align256(c * 8));
     int32_t* vals2 = reinterpret_cast<int32_t*>(ws + 256 + 2 * align256(c * 8) + align256(c * 4));
-    FID_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(counter), 1, 0ull, ctx->stream), "fill launch");
+    Prepared q;
+    FID_TRY(prepare_queries(ctx, db, j, q_dev, n_q, mode, &q, nullptr, nullptr, counter));
     const Plan pl = plan_for(ctx, j, 0, db->v.n_refs, n_q, EPI_THRESH);
     ScanParams p = make_params(db, j, pl, 0, db->v.n_refs, 0, n_q);
     p.hit_cap = cap;
@@ -1418,17 +1441,7 @@ int fid_compare_threshold(fid_ctx* ctx, const fid_db* db, const uint64_t* q_dev,
     o.hit_keys = keys;
     o.hit_cnt = vals;
     FID_TRY(run_scan(ctx, j, mode, EPI_THRESH, p, q, o, true));
-    unsigned long long total = 0;
-    FID_HIP(hipMemcpyAsync(&total, counter, sizeof total, hipMemcpyDeviceToHost, ctx->stream), "hipMemcpyAsync");
-    FID_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-    *total_host = (int64_t)total;
-    if ((int64_t)total > cap)
-        return fail(FID_EOVERFLOW, "%llu threshold hits exceed capacity %lld", total, (long long)cap);
-    uint64_t* sk;
-    int32_t* sv;
-    FID_HIP(launch_sort_hits(keys, vals, keys2, vals2, (int64_t)total, &sk, &sv, ctx->stream), "sort launch");
-    FID_HIP(launch_hits_to_csr(sk, sv, (int64_t)total, n_q, offs_dev, idx_dev, cnt_dev, ctx->stream), "csr launch");
-    return FID_OK;
+    return finish_hits(ctx, counter, keys, vals, keys2, vals2, cap, n_q, offs_dev, idx_dev, cnt_dev, total_host);
 }
 
 // Threshold hits and top-k of the same queries in one pass over the
@@ -1487,8 +1500,9 @@ int fid_compare_threshold_topk(fid_ctx* ctx, const fid_db* db, const uint64_t* q
                                      hidx_dev, hcnt_dev, total_host);
     }
     FID_TRY(set_device(ctx));
+    unsigned long long* counter = reinterpret_cast<unsigned long long*>(hw);
     Prepared q;
-    FID_TRY(prepare_queries(ctx, db, j, q_dev, n_q, mode, &q));
+    FID_TRY(prepare_queries(ctx, db, j, q_dev, n_q, mode, &q, nullptr, nullptr, counter));
     int32_t* counts = reinterpret_cast<int32_t*>(ws + L.off_counts);
     uint64_t* lists = reinterpret_cast<uint64_t*>(ws + L.off_lists);
     uint32_t* fills = reinterpret_cast<uint32_t*>(ws + L.off_fills);
@@ -1496,7 +1510,6 @@ int fid_compare_threshold_topk(fid_ctx* ctx, const fid_db* db, const uint64_t* q
     uint32_t* level = reinterpret_cast<uint32_t*>(ws + L.off_level);
     uint32_t* wit = reinterpret_cast<uint32_t*>(ws + L.off_wit);
     const size_t c = (size_t)(cap > 0 ? cap : 1);
-    unsigned long long* counter = reinterpret_cast<unsigned long long*>(hw);
     uint64_t* keys = reinterpret_cast<uint64_t*>(hw + 256);
     uint64_t* keys2 = reinterpret_cast<uint64_t*>(hw + 256 + align256(c * 8));
     int32_t* vals = reinterpret_cast<int32_t*>(hw + 256 + 2 * align256(c * 8));
@@ -1506,7 +1519,6 @@ int fid_compare_threshold_topk(fid_ctx* ctx, const fid_db* db, const uint64_t* q
     FID_TRY(run_full(ctx, db, j, q, mode, 0, L.seed, 0, n_q, counts, L.seed, 0, 0, false));
     FID_HIP(launch_seed_select(counts, n_q, L.seed, k, db->v.n_loci, thr_init, level, wit, ctx->stream),
             "seed select launch");
-    FID_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(counter), 1, 0ull, ctx->stream), "fill launch");
     ScanParams p = make_params(db, j, L.plan, 0, db->v.n_refs, 0, n_q);
     p.k = k;
     p.hit_cap = cap;
@@ -1524,18 +1536,7 @@ int fid_compare_threshold_topk(fid_ctx* ctx, const fid_db* db, const uint64_t* q
     FID_HIP(launch_merge_lists(lists, fills, n_q, L.plan.list_workers, k, db->v.n_loci, cnt_dev, idx_dev,
                                ctx->stream),
             "merge launch");
-    unsigned long long total = 0;
-    FID_HIP(hipMemcpyAsync(&total, counter, sizeof total, hipMemcpyDeviceToHost, ctx->stream), "hipMemcpyAsync");
-    FID_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-    *total_host = (int64_t)total;
-    if ((int64_t)total > cap)
-        return fail(FID_EOVERFLOW, "%llu threshold hits exceed capacity %lld", total, (long long)cap);
-    uint64_t* sk;
-    int32_t* sv;
-    FID_HIP(launch_sort_hits(keys, vals, keys2, vals2, (int64_t)total, &sk, &sv, ctx->stream), "sort launch");
-    FID_HIP(launch_hits_to_csr(sk, sv, (int64_t)total, n_q, offs_dev, hidx_dev, hcnt_dev, ctx->stream),
-            "csr launch");
-    return FID_OK;
+    return finish_hits(ctx, counter, keys, vals, keys2, vals2, cap, n_q, offs_dev, hidx_dev, hcnt_dev, total_host);
 }
 
 // Threshold hits of a streamed database (the paper's host driver, Section
@@ -1652,23 +1653,11 @@ int fid_compare_threshold_streamed(fid_ctx* ctx, const uint64_t* rows_host, int6
         if (!st)
             hip(launch_offset_block_hits(counter, ends, (int32_t)b, keys, cap, r0, ctx->stream), "offset launch");
     }
-    unsigned long long total = 0;
-    if (!st) hip(hipMemcpyAsync(&total, counter, sizeof total, hipMemcpyDeviceToHost, ctx->stream), "hipMemcpyAsync");
     if (copy) hip(hipStreamSynchronize(copy), "hipStreamSynchronize");
-    hip(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-    if (!st) {
-        *total_host = (int64_t)total;
-        if ((int64_t)total > cap) {
-            st = fail(FID_EOVERFLOW, "%llu threshold hits exceed capacity %lld", total, (long long)cap);
-        } else {
-            uint64_t* sk;
-            int32_t* sv;
-            hip(launch_sort_hits(keys, vals, keys2, vals2, (int64_t)total, &sk, &sv, ctx->stream), "sort launch");
-            if (!st)
-                hip(launch_hits_to_csr(sk, sv, (int64_t)total, n_q, offs_dev, idx_dev, cnt_dev, ctx->stream),
-                    "csr launch");
-        }
-    }
+    if (!st)
+        st = finish_hits(ctx, counter, keys, vals, keys2, vals2, cap, n_q, offs_dev, idx_dev, cnt_dev, total_host);
+    else
+        (void)hipStreamSynchronize(ctx->stream);
     for (int i = 0; i < 2; ++i) {
         if (copied[i]) (void)hipEventDestroy(copied[i]);
         if (freed[i]) (void)hipEventDestroy(freed[i]);

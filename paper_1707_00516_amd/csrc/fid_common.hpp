@@ -171,14 +171,16 @@ struct SelectJob {
 // ---------------------------------------------------------------- launchers
 hipError_t launch_pack(const uint8_t* bytes, int64_t n, int32_t n_loci, int64_t ld,
                        int32_t row_words, uint64_t* out, int* bad, hipStream_t s);
-// *bad |= 1 when a per-query mode is neither FID_MODE_MIXTURE nor FID_MODE_IDENTITY.
+// *bad = 1 when a per-query mode is neither FID_MODE_MIXTURE nor FID_MODE_IDENTITY.
 hipError_t launch_check_modes(const int32_t* modes, int32_t n, int* bad, hipStream_t s);
 hipError_t launch_db_build(const uint64_t* rows, int64_t n_refs, int32_t row_words,
                            int32_t n_loci, uint4* words, int32_t* pc, int32_t w4, int64_t nblk,
                            hipStream_t s);
+// clear (optional) is set to 0 on the way: a hit counter that the scan after
+// the staging counts up.
 hipError_t launch_stage_queries(const uint64_t* q, int32_t n_q, int32_t row_words,
                                 int32_t n_loci, int mode, const int32_t* qmode, uint32_t* out,
-                                int32_t qw, hipStream_t s);
+                                int32_t qw, hipStream_t s, uint64_t* clear = nullptr);
 hipError_t launch_scan(int mode, int nw, int epi, bool chunked, int rpl, const ScanParams& p,
                        const ScanBuffers& b, hipStream_t s);
 hipError_t launch_mfma_scan(int mode, int epi, const ScanParams& p, const MfmaBuffers& b,
@@ -199,7 +201,7 @@ hipError_t launch_fp4_scan(int mode, int epi, const ScanParams& p, const MfmaBuf
 // both signs.
 hipError_t launch_expand_queries_fp4(const uint64_t* q, int32_t n_q, int32_t row_words,
                                      int32_t n_loci, int mode, const int32_t* qmode, uint8_t* qx,
-                                     int32_t kpad, int32_t* pcq, hipStream_t s);
+                                     int32_t kpad, int32_t* pcq, hipStream_t s, uint64_t* clear = nullptr);
 int fp4_kpad(int32_t n_loci);
 int fp4_max_kpad();
 int fp4_refs_per_wg();
@@ -236,6 +238,13 @@ hipError_t launch_sort_hits(uint64_t* keys, int32_t* vals, uint64_t* keys2, int3
                             int64_t n, uint64_t** out_keys, int32_t** out_vals, hipStream_t s);
 hipError_t launch_hits_to_csr(const uint64_t* keys, const int32_t* vals, int64_t n, int32_t n_q,
                               int64_t* offs, int64_t* idx, int32_t* cnt, hipStream_t s);
+// Hits to CSR in one launch that reads their number from the scan's counter
+// n_dev and stores it to n_host (host memory): done when it is at most
+// small_hits_max(n_q) and cap, else the outputs are untouched.
+int64_t small_hits_max(int32_t n_q);
+hipError_t launch_small_hits(const uint64_t* keys, const int32_t* vals, const unsigned long long* n_dev, int64_t cap,
+                             int32_t n_q, int64_t* offs, int64_t* idx, int32_t* cnt, unsigned long long* n_host,
+                             hipStream_t s);
 
 // Genotype rows (0/1/2 per locus) -> 1-bit rows of 2 n_loci loci (two planes).
 hipError_t launch_pack_genotypes(const uint8_t* geno, int64_t n, int32_t n_loci, int64_t ld, int32_t row_words,

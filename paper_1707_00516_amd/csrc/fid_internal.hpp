@@ -13,11 +13,12 @@ struct fid_ctx {
     hipStream_t stream;
     int num_cus;
     int backend;         // fid_backend
-    void* scratch;       // status words, staged or expanded queries
+    void* scratch;       // staged or expanded queries
     size_t scratch_bytes;
     bool timing;         // record events around each call's main scan kernel
     std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
     size_t events_used;
+    unsigned long long* host_word;  // pinned: what a kernel tells a call that waits for it
     void* fixed_scratch;  // this device's address of the library's fixed scratch array
 };
 

@@ -18,6 +18,7 @@
 //     matrix / tiles), a filter into per-worker top-k lists, or a threshold
 //     hit append; the query x reference matrix is never written for top-k or
 //     threshold output (the reduction-on-GPU Section IV proposes).
+#include <algorithm>
 #include <type_traits>
 
 #include "fid_device.hpp"
@@ -69,7 +70,7 @@ __global__ void pack_kernel(const uint8_t* __restrict__ bytes, int64_t n, int32_
             }
         }
         out[t] = word;
-        if (badbits) atomicOr(bad, 1);
+        if (badbits) *bad = 1;
     }
 }
 
@@ -78,7 +79,7 @@ __global__ void check_modes_kernel(const int32_t* __restrict__ modes, int32_t n,
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int32_t m = modes[i];
-        if (m != FID_MODE_MIXTURE && m != FID_MODE_IDENTITY) atomicOr(bad, 1);
+        if (m != FID_MODE_MIXTURE && m != FID_MODE_IDENTITY) *bad = 1;
     }
 }
 
@@ -213,8 +214,9 @@ hipError_t launch_db_build(const uint64_t* rows, int64_t n_refs, int32_t row_wor
 // Eq. 1 becomes a plain AND: (R ^ Q) & R == R & ~Q.
 __global__ void stage_kernel(const uint64_t* __restrict__ q, int32_t n_q, int32_t row_words,
                              int32_t n_loci, int mode, const int32_t* __restrict__ qmode,
-                             uint32_t* __restrict__ out, int32_t qw)
+                             uint32_t* __restrict__ out, int32_t qw, uint64_t* __restrict__ clear)
 {
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0ull;
     const int64_t total = (int64_t)n_q * qw;
     const int32_t l32 = (n_loci + 31) / 32;
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
@@ -233,14 +235,14 @@ __global__ void stage_kernel(const uint64_t* __restrict__ q, int32_t n_q, int32_
 
 hipError_t launch_stage_queries(const uint64_t* q, int32_t n_q, int32_t row_words,
                                 int32_t n_loci, int mode, const int32_t* qmode, uint32_t* out,
-                                int32_t qw, hipStream_t s)
+                                int32_t qw, hipStream_t s, uint64_t* clear)
 {
     const int64_t total = (int64_t)n_q * qw;
     int64_t blocks = (total + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(stage_kernel, dim3((unsigned)blocks), dim3(256), 0, s, q, n_q, row_words,
-                       n_loci, mode, qmode, out, qw);
+                       n_loci, mode, qmode, out, qw, clear);
     return hipGetLastError();
 }
 
@@ -890,6 +892,70 @@ hipError_t launch_hits_to_csr(const uint64_t* keys, const int32_t* vals, int64_t
     if (blocks > 65536) blocks = 65536;
     hipLaunchKernelGGL(csr_values_kernel, dim3((unsigned)blocks), dim3(256), 0, s, keys, vals, n,
                        idx, cnt);
+    return hipGetLastError();
+}
+
+// Few hits: one launch in place of the sort, its merge passes and the two CSR
+// kernels.  A hit's place is the number of smaller keys (keys are unique) and
+// a query's offset the number of keys below it, both counted against all keys
+// in LDS: a wave per quarter of the keys, a lane per hit or query.  Bound:
+// latency; 300 hits take 5 us where the sort of one 2048-key tile took 41 and
+// the CSR kernels 9.  n_dev is the scan's own counter, so that the launch can
+// follow the scan without the host knowing it; a total beyond the kernel's or
+// the caller's capacity leaves the outputs to the caller.
+constexpr int kSmallHits = 4096;
+constexpr int kSmallHitThreads = 256;
+
+__global__ __launch_bounds__(kSmallHitThreads) void hits_csr_small_kernel(
+    const uint64_t* __restrict__ keys, const int32_t* __restrict__ vals,
+    const unsigned long long* __restrict__ n_dev, int64_t cap, int32_t n_q, int64_t* __restrict__ offs,
+    int64_t* __restrict__ idx, int32_t* __restrict__ cnt, unsigned long long* __restrict__ n_host)
+{
+    __shared__ uint64_t s[kSmallHits];
+    __shared__ int below[64];
+    const unsigned long long total = *n_dev;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (blockIdx.x == 0 && tid == 0) *n_host = total;
+    if (cap < 0 || total > (unsigned long long)min(cap, (int64_t)kSmallHits)) return;
+    const int n = (int)total;
+    const int kb = (n_q + 64) / 64;                  // blocks of 64 queries (n_q + 1 offsets)
+    const bool of_query = (int)blockIdx.x < kb;
+    const int item = (of_query ? (int)blockIdx.x : (int)blockIdx.x - kb) * 64 + lane;
+    if (!of_query && ((int)blockIdx.x - kb) * 64 >= n) return;
+    for (int i = tid; i < n; i += kSmallHitThreads) s[i] = keys[i];
+    if (tid < 64) below[tid] = 0;
+    __syncthreads();
+    const uint64_t key = of_query ? (uint64_t)item << kIdxBits : item < n ? s[item] : 0ull;
+    const int j1 = n * (wv + 1) / 4;
+    int c = 0;
+#pragma unroll 4
+    for (int j = n * wv / 4; j < j1; ++j) c += s[j] < key ? 1 : 0;
+    atomicAdd(&below[lane], c);
+    __syncthreads();
+    if (wv != 0) return;
+    if (of_query) {
+        if (item <= n_q) offs[item] = below[lane];
+    } else if (item < n) {
+        idx[below[lane]] = (int64_t)(key & kIdxMask);
+        cnt[below[lane]] = vals[item];
+    }
+}
+
+// Queries whose offsets the one launch counts too (a block per 64).
+constexpr int32_t kSmallHitMaxQ = 8192;
+
+int64_t small_hits_max(int32_t n_q) { return n_q <= kSmallHitMaxQ ? kSmallHits : -1; }
+
+hipError_t launch_small_hits(const uint64_t* keys, const int32_t* vals, const unsigned long long* n_dev, int64_t cap,
+                             int32_t n_q, int64_t* offs, int64_t* idx, int32_t* cnt, unsigned long long* n_host,
+                             hipStream_t s)
+{
+    // (a call whose queries are beyond the kernel's only learns the total)
+    const bool small = n_q <= kSmallHitMaxQ;
+    const unsigned blocks =
+        small ? (unsigned)((n_q + 64) / 64 + std::min<int64_t>(std::max<int64_t>(cap, 0), kSmallHits) / 64 + 1) : 1u;
+    hipLaunchKernelGGL(hits_csr_small_kernel, dim3(blocks), dim3(kSmallHitThreads), 0, s, keys, vals, n_dev,
+                       small ? cap : (int64_t)-1, n_q, offs, idx, cnt, n_host);
     return hipGetLastError();
 }
 

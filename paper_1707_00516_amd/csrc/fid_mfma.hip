@@ -1243,8 +1243,10 @@ constexpr int kExpandWaves = 4;
 // element order above (zero past the row), plus popcount(Q_q).
 __global__ __launch_bounds__(64 * kExpandWaves) void expand_queries_fp4_kernel(
     const uint64_t* __restrict__ q, int32_t n_q, int32_t row_words, int32_t n_loci, int mode,
-    const int32_t* __restrict__ qmode, uint8_t* __restrict__ qx, int32_t kpad, int32_t* __restrict__ pcq)
+    const int32_t* __restrict__ qmode, uint8_t* __restrict__ qx, int32_t kpad, int32_t* __restrict__ pcq,
+    uint64_t* __restrict__ clear)
 {
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0ull;
     const int64_t i = (int64_t)blockIdx.x * kExpandWaves + (threadIdx.x >> 6);
     if (i >= n_q) return;
     const int md = mode == kModePerQuery ? qmode[i] : mode;
@@ -1253,11 +1255,11 @@ __global__ __launch_bounds__(64 * kExpandWaves) void expand_queries_fp4_kernel(
 
 hipError_t launch_expand_queries_fp4(const uint64_t* q, int32_t n_q, int32_t row_words,
                                      int32_t n_loci, int mode, const int32_t* qmode, uint8_t* qx,
-                                     int32_t kpad, int32_t* pcq, hipStream_t s)
+                                     int32_t kpad, int32_t* pcq, hipStream_t s, uint64_t* clear)
 {
     const unsigned blocks = (unsigned)((n_q + kExpandWaves - 1) / kExpandWaves);
     hipLaunchKernelGGL(expand_queries_fp4_kernel, dim3(blocks), dim3(64 * kExpandWaves), 0, s, q, n_q,
-                       row_words, n_loci, mode, qmode, qx, kpad, pcq);
+                       row_words, n_loci, mode, qmode, qx, kpad, pcq, clear);
     return hipGetLastError();
 }
 

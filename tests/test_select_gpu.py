@@ -41,3 +41,34 @@ def test_selection_edges(ctx, n_refs, L, n_q, k, kinds):
         wc, wi = oracle.topk(oracle.counts(refs, Q, m), k)
         assert np.array_equal(cnt.cpu().numpy(), wc) and np.array_equal(idx.cpu().numpy(), wi)
     db.close()
+
+
+@pytest.mark.parametrize("n_refs,n_q,hits", [(100, 3, 0), (1, 1, 1), (4096, 1, 4096), (4097, 1, 4097), (64, 65, 4160),
+                                             (1, 8192, 8192), (1, 8193, 0), (3, 8300, 24900), (50, 64, 3200)])
+def test_threshold_hits_csr_edges(ctx, n_refs, n_q, hits):
+    """Hits put in order by one launch (at most 4096 of at most 8192 queries)
+    and by the sort; every reference of every query is a hit, or none."""
+    log(f"hits n_refs={n_refs} n_q={n_q} hits={hits}")
+    from paper_1707_00516_amd.torch_api import FidError
+    rng = np.random.default_rng(hits)
+    L = 90
+    refs = np.ones((n_refs, L), np.uint8)
+    Q = (rng.random((n_q, L)) < 0.5).astype(np.uint8)
+    db, q = db_from_bytes(ctx, refs), pack_rows(ctx, Q)
+    w = oracle.counts(refs, Q, oracle.MIXTURE)
+    t = L if hits else -1
+    for cap in {max(hits, 1), hits + 5000}:
+        got = [x.cpu().numpy() for x in ctx.compare_threshold(db, q, oracle.MIXTURE, t, cap=cap)]
+        assert all(np.array_equal(a, b) for a, b in zip(got, oracle.threshold(w, np.full(n_q, t, np.int32))))
+    if hits > 1:  # one too many for the caller's buffers: the total comes back
+        from paper_1707_00516_amd import FID_EOVERFLOW, fid_compare_threshold, fid_threshold_workspace_bytes
+        cap = hits - 1
+        thr = torch.full((n_q,), t, dtype=torch.int32, device="cuda")
+        ws = torch.empty(fid_threshold_workspace_bytes(db.handle, n_q, cap), dtype=torch.uint8, device="cuda")
+        offs, idx = (torch.empty(n, dtype=torch.int64, device="cuda") for n in (n_q + 1, cap))
+        cnt = torch.empty(cap, dtype=torch.int32, device="cuda")
+        with pytest.raises(FidError) as e:
+            fid_compare_threshold(ctx.handle, db.handle, q.data_ptr(), n_q, oracle.MIXTURE, thr.data_ptr(),
+                                  ws.data_ptr(), ws.numel(), cap, offs.data_ptr(), idx.data_ptr(), cnt.data_ptr())
+        assert e.value.status == FID_EOVERFLOW and e.value.needed == hits
+    db.close()
