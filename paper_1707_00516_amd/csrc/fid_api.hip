@@ -95,6 +95,40 @@ int fixed_scratch_address(int device, void** out)
     return FID_OK;
 }
 
+// Pinned words for contexts, 64 bytes apart in one page that the first context
+// allocates and the process keeps (a pinned allocation per context would cost
+// it 0.2 ms).  A context gives its word back; with all in use, the next gets an
+// allocation of its own.
+constexpr int kHostWords = 64;
+std::mutex g_words_mu;
+char* g_words = nullptr;
+uint64_t g_words_used = 0;
+
+int take_host_word(unsigned long long** out)
+{
+    std::lock_guard<std::mutex> lk(g_words_mu);
+    if (!g_words)
+        FID_HIP(hipHostMalloc(reinterpret_cast<void**>(&g_words), 64 * kHostWords, hipHostMallocPortable),
+                "hipHostMalloc");
+    if (~g_words_used) {
+        const int i = __builtin_ctzll(~g_words_used);
+        g_words_used |= 1ull << i;
+        *out = reinterpret_cast<unsigned long long*>(g_words + 64 * i);
+        return FID_OK;
+    }
+    FID_HIP(hipHostMalloc(reinterpret_cast<void**>(out), 64, hipHostMallocPortable), "hipHostMalloc");
+    return FID_OK;
+}
+
+void give_host_word(unsigned long long* w)
+{
+    if (!w) return;
+    std::lock_guard<std::mutex> lk(g_words_mu);
+    char* const p = reinterpret_cast<char*>(w);
+    if (p >= g_words && p < g_words + 64 * kHostWords) g_words_used &= ~(1ull << ((p - g_words) / 64));
+    else (void)hipHostFree(w);
+}
+
 }  // namespace
 
 namespace {
@@ -566,6 +600,21 @@ int finish_hits(fid_ctx* ctx, const unsigned long long* counter, uint64_t* keys,
     return FID_OK;
 }
 
+// The context's first n copy streams and m events.  Successive blocks are
+// copied on two streams in turn: a stream starts a copy up to 0.45 ms after
+// its last one has ended, which the other stream's copy fills (1M x 2048 loci
+// in eight blocks: 8.3 ms per call on one stream, PCIe moves them in 4.5).
+int ensure_copy_streams(fid_ctx* ctx, int n, int m)
+{
+    for (int i = 0; i < n; ++i)
+        if (!ctx->copy_stream[i])
+            FID_HIP(hipStreamCreateWithFlags(&ctx->copy_stream[i], hipStreamNonBlocking), "hipStreamCreate");
+    for (int i = 0; i < m; ++i)
+        if (!ctx->copy_event[i])
+            FID_HIP(hipEventCreateWithFlags(&ctx->copy_event[i], hipEventDisableTiming), "hipEventCreate");
+    return FID_OK;
+}
+
 int check_range(const fid_db* db, int64_t r_lo, int64_t r_hi)
 {
     if (r_lo < 0 || r_hi <= r_lo || r_hi > db->v.n_refs)
@@ -770,12 +819,9 @@ int fid_ctx_create(fid_ctx** out, int device, void* stream)
     c->fixed_scratch = nullptr;
     c->host_word = nullptr;
     int st = fixed_scratch_address(device, &c->fixed_scratch);
-    if (!st) {
-        e = hipHostMalloc(reinterpret_cast<void**>(&c->host_word), 64, hipHostMallocDefault);
-        if (e != hipSuccess) st = fail(FID_ENOMEM, "pinned allocation failed: %s", hipGetErrorString(e));
-    }
+    if (!st) st = take_host_word(&c->host_word);
     if (st) {
-        if (c->host_word) (void)hipHostFree(c->host_word);
+        give_host_word(c->host_word);
         delete c;
         return st;
     }
@@ -790,7 +836,11 @@ int fid_ctx_destroy(fid_ctx* ctx)
     if (!st) {
         hipStreamSynchronize(ctx->stream);
         if (ctx->scratch) hipFree(ctx->scratch);
-        if (ctx->host_word) hipHostFree(ctx->host_word);
+        give_host_word(ctx->host_word);
+        for (hipStream_t cs : ctx->copy_stream)
+            if (cs) hipStreamDestroy(cs);
+        for (hipEvent_t ev : ctx->copy_event)
+            if (ev) hipEventDestroy(ev);
         for (auto& ev : ctx->events) {
             hipEventDestroy(ev.first);
             hipEventDestroy(ev.second);
@@ -1159,32 +1209,29 @@ int fid_compare_topk_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
     int32_t* tcnt = reinterpret_cast<int32_t*>(ws + L.off_tcnt);
     int64_t* tidx = reinterpret_cast<int64_t*>(ws + L.off_tidx);
 
-    hipStream_t copy = nullptr;
-    hipEvent_t copied[2] = {nullptr, nullptr}, freed[2] = {nullptr, nullptr};
+    FID_TRY(ensure_copy_streams(ctx, 2, 4));
+    const hipStream_t* const copy = ctx->copy_stream;
+    const hipEvent_t copied[2] = {ctx->copy_event[0], ctx->copy_event[1]};
+    const hipEvent_t freed[2] = {ctx->copy_event[2], ctx->copy_event[3]};
     int st = FID_OK;
     auto hip = [&](hipError_t e, const char* what) {
         if (e != hipSuccess && !st) st = hip_fail(e, what);
     };
-    hip(hipStreamCreateWithFlags(&copy, hipStreamNonBlocking), "hipStreamCreate");
-    for (int i = 0; i < 2 && !st; ++i) {
-        hip(hipEventCreateWithFlags(&copied[i], hipEventDisableTiming), "hipEventCreate");
-        hip(hipEventCreateWithFlags(&freed[i], hipEventDisableTiming), "hipEventCreate");
-    }
     if (!st) hip(launch_reset_running(nullptr, n_q, k, running, bound, ctx->stream), "reset launch");
-    // the copy stream starts after everything already queued on the context
+    // the copy streams start after everything already queued on the context
     if (!st) hip(hipEventRecord(freed[1], ctx->stream), "hipEventRecord");
-    if (!st) hip(hipStreamWaitEvent(copy, freed[1], 0), "hipStreamWaitEvent");
+    for (int i = 0; i < 2 && !st; ++i) hip(hipStreamWaitEvent(copy[i], freed[1], 0), "hipStreamWaitEvent");
     for (int64_t b = 0; b < n_blocks && !st; ++b) {
         const int slot = (int)(b & 1);
         const int64_t r0 = b * blk;
         const int64_t n = std::min(blk, n_refs - r0);
         uint64_t* stage = reinterpret_cast<uint64_t*>(ws + L.off_stage[slot]);
         // block b's copy waits until block b - 2 has been built from this slot
-        if (b >= 2) hip(hipStreamWaitEvent(copy, freed[slot], 0), "hipStreamWaitEvent");
+        if (b >= 2) hip(hipStreamWaitEvent(copy[slot], freed[slot], 0), "hipStreamWaitEvent");
         if (!st)
             hip(hipMemcpyAsync(stage, rows_host + r0 * rw, (size_t)n * (size_t)rw * sizeof(uint64_t),
-                               hipMemcpyHostToDevice, copy), "block copy");
-        if (!st) hip(hipEventRecord(copied[slot], copy), "hipEventRecord");
+                               hipMemcpyHostToDevice, copy[slot]), "block copy");
+        if (!st) hip(hipEventRecord(copied[slot], copy[slot]), "hipEventRecord");
         if (!st) hip(hipStreamWaitEvent(ctx->stream, copied[slot], 0), "hipStreamWaitEvent");
         if (st) break;
         fid_db* db = nullptr;
@@ -1200,13 +1247,8 @@ int fid_compare_topk_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
     }
     if (!st) hip(launch_finalize_topk(running, nullptr, n_q, k, k, cnt_dev, idx_dev, ctx->stream), "finalize launch");
     // the host rows must stay untouched until every copy has run
-    if (copy) hip(hipStreamSynchronize(copy), "hipStreamSynchronize");
+    for (int i = 0; i < 2; ++i) hip(hipStreamSynchronize(copy[i]), "hipStreamSynchronize");
     hip(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-    for (int i = 0; i < 2; ++i) {
-        if (copied[i]) (void)hipEventDestroy(copied[i]);
-        if (freed[i]) (void)hipEventDestroy(freed[i]);
-    }
-    if (copy) (void)hipStreamDestroy(copy);
     return st;
 }
 
@@ -1274,25 +1316,19 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
     const int64_t blk = std::min(block_refs, n_refs);
     const int64_t n_blocks = (n_refs + blk - 1) / blk;
 
-    hipStream_t h2d = nullptr, d2h = nullptr;
-    hipEvent_t copied[2] = {}, built[2] = {}, counted[2] = {}, shipped[2] = {}, start = nullptr;
+    FID_TRY(ensure_copy_streams(ctx, 4, 9));
+    const hipStream_t* const h2d = ctx->copy_stream;
+    const hipStream_t* const d2h = ctx->copy_stream + 2;
+    const hipEvent_t* const ev = ctx->copy_event;
+    const hipEvent_t copied[2] = {ev[0], ev[1]}, built[2] = {ev[2], ev[3]}, counted[2] = {ev[4], ev[5]},
+                     shipped[2] = {ev[6], ev[7]}, start = ev[8];
     int st = FID_OK;
     auto hip = [&](hipError_t e, const char* what) {
         if (e != hipSuccess && !st) st = hip_fail(e, what);
     };
-    hip(hipStreamCreateWithFlags(&h2d, hipStreamNonBlocking), "hipStreamCreate");
-    hip(hipStreamCreateWithFlags(&d2h, hipStreamNonBlocking), "hipStreamCreate");
-    hip(hipEventCreateWithFlags(&start, hipEventDisableTiming), "hipEventCreate");
-    for (int i = 0; i < 2 && !st; ++i) {
-        hip(hipEventCreateWithFlags(&copied[i], hipEventDisableTiming), "hipEventCreate");
-        hip(hipEventCreateWithFlags(&built[i], hipEventDisableTiming), "hipEventCreate");
-        hip(hipEventCreateWithFlags(&counted[i], hipEventDisableTiming), "hipEventCreate");
-        hip(hipEventCreateWithFlags(&shipped[i], hipEventDisableTiming), "hipEventCreate");
-    }
-    // both copy streams start after everything already queued on the context
-    if (!st) hip(hipEventRecord(start, ctx->stream), "hipEventRecord");
-    if (!st) hip(hipStreamWaitEvent(h2d, start, 0), "hipStreamWaitEvent");
-    if (!st) hip(hipStreamWaitEvent(d2h, start, 0), "hipStreamWaitEvent");
+    // the copy streams start after everything already queued on the context
+    hip(hipEventRecord(start, ctx->stream), "hipEventRecord");
+    for (int i = 0; i < 4 && !st; ++i) hip(hipStreamWaitEvent(ctx->copy_stream[i], start, 0), "hipStreamWaitEvent");
     for (int64_t b = 0; b < n_blocks && !st; ++b) {
         const int slot = (int)(b & 1);
         const int64_t r0 = b * blk;
@@ -1300,11 +1336,11 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
         uint64_t* stage = reinterpret_cast<uint64_t*>(ws + L.off_stage[slot]);
         int32_t* out = reinterpret_cast<int32_t*>(ws + L.off_out[slot]);
         // rows in: the slot is free once block b - 2 has been built from it
-        if (b >= 2) hip(hipStreamWaitEvent(h2d, built[slot], 0), "hipStreamWaitEvent");
+        if (b >= 2) hip(hipStreamWaitEvent(h2d[slot], built[slot], 0), "hipStreamWaitEvent");
         if (!st)
             hip(hipMemcpyAsync(stage, rows_host + r0 * rw, (size_t)n * (size_t)rw * sizeof(uint64_t),
-                               hipMemcpyHostToDevice, h2d), "block copy");
-        if (!st) hip(hipEventRecord(copied[slot], h2d), "hipEventRecord");
+                               hipMemcpyHostToDevice, h2d[slot]), "block copy");
+        if (!st) hip(hipEventRecord(copied[slot], h2d[slot]), "hipEventRecord");
         // build and count: the count slot is free once block b - 2's counts shipped
         if (!st) hip(hipStreamWaitEvent(ctx->stream, copied[slot], 0), "hipStreamWaitEvent");
         if (!st && b >= 2) hip(hipStreamWaitEvent(ctx->stream, shipped[slot], 0), "hipStreamWaitEvent");
@@ -1317,23 +1353,16 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
         delete db;  // the host handle only: the launches took its view by value
         if (!st) hip(hipEventRecord(counted[slot], ctx->stream), "hipEventRecord");
         // counts out: [n_q][n] into columns [r0, r0 + n) of the caller's rows
-        if (!st) hip(hipStreamWaitEvent(d2h, counted[slot], 0), "hipStreamWaitEvent");
+        if (!st) hip(hipStreamWaitEvent(d2h[slot], counted[slot], 0), "hipStreamWaitEvent");
         if (!st)
             hip(hipMemcpy2DAsync(counts_host + r0, (size_t)ld * sizeof(int32_t), out, (size_t)n * sizeof(int32_t),
-                                 (size_t)n * sizeof(int32_t), (size_t)n_q, hipMemcpyDeviceToHost, d2h),
+                                 (size_t)n * sizeof(int32_t), (size_t)n_q, hipMemcpyDeviceToHost, d2h[slot]),
                 "counts copy");
-        if (!st) hip(hipEventRecord(shipped[slot], d2h), "hipEventRecord");
+        if (!st) hip(hipEventRecord(shipped[slot], d2h[slot]), "hipEventRecord");
     }
     // every copy has run before the host buffers are handed back
-    if (h2d) hip(hipStreamSynchronize(h2d), "hipStreamSynchronize");
-    if (d2h) hip(hipStreamSynchronize(d2h), "hipStreamSynchronize");
+    for (int i = 0; i < 4; ++i) hip(hipStreamSynchronize(ctx->copy_stream[i]), "hipStreamSynchronize");
     hip(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-    for (int i = 0; i < 2; ++i)
-        for (hipEvent_t e : {copied[i], built[i], counted[i], shipped[i]})
-            if (e) (void)hipEventDestroy(e);
-    if (start) (void)hipEventDestroy(start);
-    if (h2d) (void)hipStreamDestroy(h2d);
-    if (d2h) (void)hipStreamDestroy(d2h);
     return st;
 }
 
@@ -1601,32 +1630,29 @@ int fid_compare_threshold_streamed(fid_ctx* ctx, const uint64_t* rows_host, int6
     int32_t* vals2 = reinterpret_cast<int32_t*>(take(c * sizeof(int32_t)));
     int64_t* ends = reinterpret_cast<int64_t*>(take((size_t)(n_blocks + 1) * sizeof(int64_t)));
 
-    hipStream_t copy = nullptr;
-    hipEvent_t copied[2] = {}, freed[2] = {};
+    FID_TRY(ensure_copy_streams(ctx, 2, 4));
+    const hipStream_t* const copy = ctx->copy_stream;
+    const hipEvent_t copied[2] = {ctx->copy_event[0], ctx->copy_event[1]};
+    const hipEvent_t freed[2] = {ctx->copy_event[2], ctx->copy_event[3]};
     int st = FID_OK;
     auto hip = [&](hipError_t e, const char* what) {
         if (e != hipSuccess && !st) st = hip_fail(e, what);
     };
-    hip(hipStreamCreateWithFlags(&copy, hipStreamNonBlocking), "hipStreamCreate");
-    for (int i = 0; i < 2 && !st; ++i) {
-        hip(hipEventCreateWithFlags(&copied[i], hipEventDisableTiming), "hipEventCreate");
-        hip(hipEventCreateWithFlags(&freed[i], hipEventDisableTiming), "hipEventCreate");
-    }
     if (!st) hip(launch_fill_u64(reinterpret_cast<uint64_t*>(counter), 1, 0ull, ctx->stream), "fill launch");
     if (!st) hip(launch_fill_u64(reinterpret_cast<uint64_t*>(ends), 1, 0ull, ctx->stream), "fill launch");
     if (!st) hip(hipEventRecord(freed[1], ctx->stream), "hipEventRecord");
-    if (!st) hip(hipStreamWaitEvent(copy, freed[1], 0), "hipStreamWaitEvent");
+    for (int i = 0; i < 2 && !st; ++i) hip(hipStreamWaitEvent(copy[i], freed[1], 0), "hipStreamWaitEvent");
     Prepared q;
     Job j{};
     for (int64_t b = 0; b < n_blocks && !st; ++b) {
         const int slot = (int)(b & 1);
         const int64_t r0 = b * blk;
         const int64_t n = std::min(blk, n_refs - r0);
-        if (b >= 2) hip(hipStreamWaitEvent(copy, freed[slot], 0), "hipStreamWaitEvent");
+        if (b >= 2) hip(hipStreamWaitEvent(copy[slot], freed[slot], 0), "hipStreamWaitEvent");
         if (!st)
             hip(hipMemcpyAsync(stage[slot], rows_host + r0 * rw, (size_t)n * (size_t)rw * sizeof(uint64_t),
-                               hipMemcpyHostToDevice, copy), "block copy");
-        if (!st) hip(hipEventRecord(copied[slot], copy), "hipEventRecord");
+                               hipMemcpyHostToDevice, copy[slot]), "block copy");
+        if (!st) hip(hipEventRecord(copied[slot], copy[slot]), "hipEventRecord");
         if (!st) hip(hipStreamWaitEvent(ctx->stream, copied[slot], 0), "hipStreamWaitEvent");
         if (st) break;
         fid_db* db = nullptr;
@@ -1653,16 +1679,11 @@ int fid_compare_threshold_streamed(fid_ctx* ctx, const uint64_t* rows_host, int6
         if (!st)
             hip(launch_offset_block_hits(counter, ends, (int32_t)b, keys, cap, r0, ctx->stream), "offset launch");
     }
-    if (copy) hip(hipStreamSynchronize(copy), "hipStreamSynchronize");
+    for (int i = 0; i < 2; ++i) hip(hipStreamSynchronize(copy[i]), "hipStreamSynchronize");
     if (!st)
         st = finish_hits(ctx, counter, keys, vals, keys2, vals2, cap, n_q, offs_dev, idx_dev, cnt_dev, total_host);
     else
         (void)hipStreamSynchronize(ctx->stream);
-    for (int i = 0; i < 2; ++i) {
-        if (copied[i]) (void)hipEventDestroy(copied[i]);
-        if (freed[i]) (void)hipEventDestroy(freed[i]);
-    }
-    if (copy) (void)hipStreamDestroy(copy);
     return st;
 }
 
