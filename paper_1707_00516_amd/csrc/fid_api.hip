@@ -277,48 +277,67 @@ struct Job {
     int32_t kpad;  // MFMA: expanded query row bytes
 };
 
-// The int8 kernel holds a query tile of whole rows in LDS (rows up to
-// mfma_max_loci() loci; longer rows use the popcount scan); the fp4 kernel
-// stages long rows chunk by chunk and covers every row length.  AUTO weighs each
-// family's measured rate at 2048 x 20M x 2048 (comparisons/s relative to the
-// popcount scan: int8 x2.2, fp4 x3.2) by how full its query tiles are
-// (64 queries for int8, 128 for fp4) and takes the best.
-int resolve_backend(const fid_ctx* ctx, const fid_db* db, int32_t n_q)
+// The family a backend forces (on the context, else FASTID_BACKEND), where its
+// kernels hold rows of this length: the int8 kernel a query tile of whole rows in
+// LDS, the fp4 kernel rows of any length it can stage.  FID_BACKEND_AUTO: none.
+int forced_backend(const fid_ctx* ctx, const fid_db* db)
 {
-    const bool int8_ok = mfma_kpad(db->v.n_loci) <= mfma_max_loci();
-    const bool fp4_ok = fp4_kpad(db->v.n_loci) <= fp4_max_kpad();
     int b = ctx->backend;
     if (b == FID_BACKEND_AUTO) b = env_int("FASTID_BACKEND", FID_BACKEND_AUTO, 0, 3);
-    if (b == FID_BACKEND_MFMA_FP4 && !fp4_ok) b = FID_BACKEND_MFMA;
-    if (b == FID_BACKEND_MFMA) return int8_ok ? b : FID_BACKEND_POPCOUNT;
-    if (b == FID_BACKEND_MFMA_FP4 || b == FID_BACKEND_POPCOUNT) return b;
-    auto fill = [&](int tile) {
-        const int64_t tiles = (n_q + tile - 1) / tile;
-        return (double)n_q / (double)(tiles * tile);
-    };
-    // Rate of a full 128-query fp4 tile relative to the popcount scan, from
-    // measured crossovers (top-32 over 2M-5M references): short rows give
-    // the matrix cores little work per tile and its fixed costs dominate.
-    const int kp = fp4_kpad(db->v.n_loci);
-    const double fp4_rate = kp <= 1024 ? 2.0 : kp <= 2048 ? 5.3 : 6.0;
-    // the int8 kernel never beat the fp4 one in the measured sweeps: AUTO
-    // takes it only where the fp4 tile cannot hold the rows
-    const double r_int8 = int8_ok && !fp4_ok ? 2.2 * fill(mfma_queries_per_wg()) : 0.0;
-    const double r_fp4 = fp4_ok ? fp4_rate * fill(fp4_queries_per_wg()) : 0.0;
-    if (r_fp4 >= 1.0 && r_fp4 >= r_int8) return FID_BACKEND_MFMA_FP4;
-    if (r_int8 >= 1.0) return FID_BACKEND_MFMA;
-    return FID_BACKEND_POPCOUNT;
+    if (b == FID_BACKEND_MFMA_FP4 && fp4_kpad(db->v.n_loci) > fp4_max_kpad()) b = FID_BACKEND_MFMA;
+    if (b == FID_BACKEND_MFMA && mfma_kpad(db->v.n_loci) > mfma_max_loci()) b = FID_BACKEND_POPCOUNT;
+    return b;
 }
 
-// Per-query modes run on the fp4 or popcount kernels only.
-Job make_job(const fid_ctx* ctx, const fid_db* db, int32_t n_q, bool per_query_modes = false)
+// What a call writes decides where the families cross: every count, or the few
+// references that pass a filter.
+enum Reduce { kCounts, kFiltered };
+
+// AUTO's choice for n_q queries against n references.  The popcount scan costs
+// its queries one by one, the fp4 tile of up to 128 nearly the same whether
+// full or not, so fp4 wins from a number of queries that falls with the row
+// length.  Measured crossings in queries (all counts, at 100k-1M references):
+// under 32 up to 300 loci (100k references, 64 queries: 14.7 us against 12.6
+// at 128 loci), 11 at 1024, 4 at 2048, 3 at 4096, 2 at 16384; filtered (top-32,
+// 400k-5M references): 50, 28, 10 and 6 at 300, 1024, 2048 and 8192 loci.
+// 12288 / loci and twice that follow them (2048 loci x 400k references, top-32:
+// 32 queries 113 us popcount, 75 fp4; 4 queries 49 and 59).
+// A database of few 128-reference tiles leaves workgroups without one, and the
+// popcount scan splits finer (all counts; us popcount, fp4): 5000 x 2048 loci,
+// 256 queries 13.7, 19.2; 10k x 2048, 128 queries 13.3, 19.1; 20k x 1024, 64
+// queries 9.3, 11.6, 256 19.3, 18.2; 20k x 2048, 8 queries 9.1, 8.6; 40k x 512,
+// 128 queries 13.8, 17.4; 40k x 1024, 32 queries 9.2, 9.1.
+// The int8 kernel never beat the fp4 one: AUTO takes it only where the fp4 tile
+// cannot hold the rows, from half a tile of 64 queries.
+int resolve_backend(const fid_ctx* ctx, const fid_db* db, int64_t n, int32_t n_q, Reduce what)
+{
+    const int forced = forced_backend(ctx, db);
+    if (forced != FID_BACKEND_AUTO) return forced;
+    const int L = db->v.n_loci;
+    if (fp4_kpad(L) > fp4_max_kpad()) {
+        const int64_t tiles = (n_q + mfma_queries_per_wg() - 1) / mfma_queries_per_wg();
+        const bool int8 = mfma_kpad(L) <= mfma_max_loci() && 2.2 * n_q >= (double)(tiles * mfma_queries_per_wg());
+        return int8 ? FID_BACKEND_MFMA : FID_BACKEND_POPCOUNT;
+    }
+    int32_t least = what == kCounts ? std::clamp(12288 / L, 2, 32) : std::clamp(24576 / L, 4, 48);
+    if (n <= 8192) least = 512;
+    else if (n <= (L > 2048 ? 0 : L > 1024 ? 12288 : L > 512 ? 32768 : 49152)) least = 256;
+    else if (n <= 32768) least = std::max(least, 8);
+    return n_q >= least ? FID_BACKEND_MFMA_FP4 : FID_BACKEND_POPCOUNT;
+}
+
+Job job_of(const fid_db* db, int backend)
 {
     Job j{};
-    j.backend = resolve_backend(ctx, db, n_q);
-    if (per_query_modes && j.backend == FID_BACKEND_MFMA) j.backend = FID_BACKEND_POPCOUNT;
+    j.backend = backend;
     j.sh = shape_for(db);
-    j.kpad = j.backend == FID_BACKEND_MFMA_FP4 ? fp4_kpad(db->v.n_loci) : mfma_kpad(db->v.n_loci);
+    j.kpad = backend == FID_BACKEND_MFMA_FP4 ? fp4_kpad(db->v.n_loci) : mfma_kpad(db->v.n_loci);
     return j;
+}
+
+Job make_job(const fid_ctx* ctx, const fid_db* db, int32_t n_q, Reduce what)
+{
+    return job_of(db, resolve_backend(ctx, db, db->v.n_refs, n_q, what));
 }
 
 Plan plan_fp4(int num_cus, int64_t r_lo, int64_t r_hi, int32_t nq, int epi)
@@ -548,12 +567,13 @@ struct TopkLayout {
     size_t off_lists, off_fills, off_counts, off_thr, off_level, off_wit, total;
 };
 
+// direct: the whole range's counts, then the selection (else the list scan).
 TopkLayout topk_layout(const fid_ctx* ctx, const Job& j, int64_t r_lo, int64_t r_hi, int32_t n_q,
-                       int32_t k)
+                       int32_t k, bool direct)
 {
     TopkLayout L{};
     const int64_t n = r_hi - r_lo;
-    L.seed = seed_refs(n, j.backend, n_q);
+    L.seed = direct ? n : seed_refs(n, j.backend, n_q);
     L.direct = L.seed == n;
     size_t off = 0;
     if (L.direct) {
@@ -576,6 +596,83 @@ TopkLayout topk_layout(const fid_ctx* ctx, const Job& j, int64_t r_lo, int64_t r
     }
     L.total = off;
     return L;
+}
+
+// A range whose counts are worth writing and selecting from: two launches
+// fewer than seed, scan and merge, and no list to keep.  The counts of such a
+// call stay in the 256 MiB of last-level cache (200 MiB of them); one workgroup
+// selects per query, so a longer range is left to the scan (fp4 scans 400k x
+// 2048 loci with 1 query in 54 us with lists, 62 without; 200k: 43 and 40; 256
+// queries x 100k: 110 and 74 us, 512: 160 and 127, 1024: 219 and 327.
+// Popcount, whose lists cost it less: 100k, 1 query 26 and 24 us, 256 175 and
+// 158; 200k, 1 query 32 and 37).
+constexpr int64_t kDirectCounts = (int64_t)50 << 20;
+
+bool direct_pays(int backend, int64_t n, int32_t n_q)
+{
+    const int64_t longest = backend == FID_BACKEND_MFMA_FP4 ? 262144 : backend == FID_BACKEND_POPCOUNT ? 131072 : 0;
+    return n <= longest && n * n_q <= kDirectCounts;
+}
+
+// A top-k call's family and layout: what is fastest of what fits.  A workspace
+// too small for all counts holds the lists, and one that was sized for the
+// popcount scan (a call with another number of queries) still serves it, so
+// that a workspace kept for several calls is not refused.
+struct TopkPick {
+    Job j;
+    TopkLayout L;
+    size_t query_bytes;  // staged queries
+};
+
+size_t query_bytes_of(const Job& j, int32_t n_q)
+{
+    if (j.backend == FID_BACKEND_MFMA_FP4) return align256((size_t)n_q * (j.kpad / 2)) + (size_t)n_q * 4;
+    if (j.backend == FID_BACKEND_MFMA) return align256((size_t)n_q * j.kpad) + (size_t)n_q * 4;
+    return (size_t)n_q * j.sh.qw * sizeof(uint32_t);
+}
+
+enum TopkUse {
+    kTopk,          // the whole answer from this range
+    kTopkScan,      // list scan preferred: with a caller's bound, or with hits in the same pass
+    kTopkPerQuery,  // modes per query: on the fp4 or popcount kernels only
+    kTopkPerQueryScan
+};
+
+TopkPick pick_topk(const fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, int32_t n_q, int32_t k,
+                   TopkUse use, size_t avail, bool with_queries = false)
+{
+    const int64_t n = r_hi - r_lo;
+    const bool per_query = use == kTopkPerQuery || use == kTopkPerQueryScan;
+    const bool scan = use == kTopkScan || use == kTopkPerQueryScan;
+    int b = resolve_backend(ctx, db, n, n_q,
+                            !scan && direct_pays(FID_BACKEND_MFMA_FP4, n, n_q) ? kCounts : kFiltered);
+    if (per_query && b == FID_BACKEND_MFMA) b = FID_BACKEND_POPCOUNT;
+    TopkPick p{}, first{};
+    auto fits = [&](int backend, bool direct) {
+        p.j = job_of(db, backend);
+        p.L = topk_layout(ctx, p.j, r_lo, r_hi, n_q, k, direct);
+        p.query_bytes = align256(query_bytes_of(p.j, n_q));
+        return p.L.total + (with_queries ? p.query_bytes : 0) <= avail;
+    };
+    if (!scan && direct_pays(b, n, n_q) && fits(b, true)) return p;
+    if (fits(b, false)) return p;
+    first = p;
+    if (b == FID_BACKEND_MFMA_FP4 && forced_backend(ctx, db) == FID_BACKEND_AUTO &&
+        fits(FID_BACKEND_POPCOUNT, false))
+        return p;
+    // a workspace sized by a call without a bound
+    if (scan && !with_queries && direct_pays(b, n, n_q) && fits(b, true)) return p;
+    return first;
+}
+
+// Workspace bytes with which a call of this use takes its fastest path, with
+// or without a bound.
+size_t topk_bytes(const fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, int32_t n_q, int32_t k,
+                  bool per_query)
+{
+    const size_t any = ~(size_t)0 >> 1;
+    return std::max(pick_topk(ctx, db, r_lo, r_hi, n_q, k, per_query ? kTopkPerQuery : kTopk, any).L.total,
+                    pick_topk(ctx, db, r_lo, r_hi, n_q, k, per_query ? kTopkPerQueryScan : kTopkScan, any).L.total);
 }
 
 // The scan's hits (keys, vals; their number at `counter`) to CSR.  Waits for the
@@ -645,11 +742,12 @@ int check_modes_dev(fid_ctx* ctx, const int32_t* modes_dev, int32_t n_q)
 // mode may be kModePerQuery with qmode[n_q] (device) giving each query's mode.
 // bound_dev (optional, device [n_q]): a caller-known exclusive bound per query
 // ("count < bound" loses nothing); with seed = false it replaces the seed
-// pass, with seed = true the tighter of the two filters.
+// pass, with seed = true the tighter of the two filters.  qarea: where the
+// staged queries of `given`, the caller's pick, go.
 int topk_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const uint64_t* q_dev,
                int32_t n_q, int mode, int32_t k, void* ws_dev, size_t ws_bytes, int32_t* cnt_dev,
                int64_t* idx_dev, const int32_t* qmode = nullptr, const uint32_t* bound_dev = nullptr,
-               bool seed = true, char* qarea = nullptr, bool timed = true)
+               bool seed = true, char* qarea = nullptr, bool timed = true, const TopkPick* given = nullptr)
 {
     const bool per_query = mode == kModePerQuery;
     FID_TRY(check_common(ctx, db, q_dev, n_q, per_query ? FID_MODE_MIXTURE : mode));
@@ -658,8 +756,10 @@ int topk_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const
     if (k < 1 || k > kMaxK) return fail(FID_EINVAL, "k=%d out of [1, %d]", k, kMaxK);
     if (!cnt_dev || !idx_dev || !ws_dev) return fail(FID_EINVAL, "NULL buffer");
     if (!aligned16(ws_dev)) return fail(FID_EINVAL, "workspace not 16-byte aligned");
-    const Job j = make_job(ctx, db, n_q, per_query);
-    const TopkLayout L = topk_layout(ctx, j, r_lo, r_hi, n_q, k);
+    const TopkUse use = per_query ? (bound_dev ? kTopkPerQueryScan : kTopkPerQuery) : (bound_dev ? kTopkScan : kTopk);
+    const TopkPick pick = given ? *given : pick_topk(ctx, db, r_lo, r_hi, n_q, k, use, ws_bytes);
+    const Job& j = pick.j;
+    const TopkLayout& L = pick.L;
     if (ws_bytes < L.total) return fail(FID_ENOMEM, "workspace %zu bytes < required %zu", ws_bytes, L.total);
     FID_TRY(set_device(ctx));
     Prepared q;
@@ -724,7 +824,7 @@ int thresh_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, con
     FID_TRY(check_range(db, r_lo, r_hi));
     if (!thr_dev || !counter || (cap > 0 && (!keys || !vals))) return fail(FID_EINVAL, "NULL buffer");
     FID_TRY(set_device(ctx));
-    const Job j = make_job(ctx, db, n_q);
+    const Job j = make_job(ctx, db, n_q, kFiltered);
     Prepared q;
     FID_TRY(prepare_queries(ctx, db, j, q_dev, n_q, mode, &q));
     const Plan pl = plan_for(ctx, j, r_lo, r_hi, n_q, EPI_THRESH);
@@ -742,31 +842,32 @@ int scratch_reserve(fid_ctx* ctx, size_t bytes) { return ensure_scratch(ctx, byt
 
 int64_t seed_prefix(int64_t n_refs, int backend, int32_t n_q) { return seed_refs(n_refs, backend, n_q); }
 
-int auto_family(const fid_ctx* ctx, const fid_db* db, int32_t n_q) { return resolve_backend(ctx, db, n_q); }
+size_t topk_scan_bytes(const fid_ctx* ctx, const fid_db* db, int32_t n_q, int32_t k, bool least)
+{
+    size_t best = 0;
+    for (const TopkUse use : {kTopkScan, kTopkPerQueryScan}) {
+        const size_t any = ~(size_t)0 >> 1;
+        size_t b = pick_topk(ctx, db, 0, db->v.n_refs, n_q, k, use, any).L.total;
+        if (least) b = std::min(b, pick_topk(ctx, db, 0, db->v.n_refs, n_q, k, use, b - 1).L.total);
+        best = std::max(best, b);
+    }
+    return best;
+}
 
-// Inside a ragged batch a job either shares the persistent popcount launch
-// (no per-job cost) or runs as its own matrix-core top-k call (a fixed cost
-// for its seed, merge and launches).  The persistent launch hides the small
-// jobs' fixed costs, so the batch routes a job only when a full query tile
-// of the matrix cores beats the popcount scan by the query-tile fill: fp4
-// rate 3.2 (rows <= 2048 loci) or 2.6 (chunked rows) times the fill, as
-// measured on the 400-job ragged batch (413 ms against 425-434 ms for the
-// per-call crossovers or a per-job cost model).  A backend forced on the
-// context is honoured as it is.
-// A batch job runs as a per-call matrix-core top-k exactly when a single call
-// would (the routed calls overlap one another on the batch's streams, which
-// hides their fixed costs as well as the persistent launch would).
+// The family of a large enough call on db, and of a call with n_q queries.
+int auto_family(const fid_ctx* ctx, const fid_db* db)
+{
+    return resolve_backend(ctx, db, kMaxRefs, kMaxQueries, kFiltered);
+}
+
 bool batch_routes_to_matrix_cores(const fid_ctx* ctx, const fid_db* db, int32_t n_q)
 {
-    return resolve_backend(ctx, db, n_q) != FID_BACKEND_POPCOUNT;
+    return resolve_backend(ctx, db, db->v.n_refs, n_q, kFiltered) != FID_BACKEND_POPCOUNT;
 }
 
 size_t query_scratch_bytes(const fid_ctx* ctx, const fid_db* db, int32_t n_q)
 {
-    const Job j = make_job(ctx, db, n_q);
-    if (j.backend == FID_BACKEND_MFMA_FP4) return align256((size_t)n_q * (j.kpad / 2)) + (size_t)n_q * 4;
-    if (j.backend == FID_BACKEND_MFMA) return align256((size_t)n_q * j.kpad) + (size_t)n_q * 4;
-    return (size_t)n_q * j.sh.qw * sizeof(uint32_t);
+    return query_bytes_of(make_job(ctx, db, n_q, kFiltered), n_q);
 }
 
 }  // namespace fid
@@ -863,7 +964,7 @@ int fid_backend_for(fid_ctx* ctx, const fid_db* db, int32_t n_q, int* backend)
 {
     if (!ctx || !db || !backend) return fail(FID_EINVAL, "NULL argument");
     if (n_q < 1 || n_q > kMaxQueries) return fail(FID_EINVAL, "n_q out of range");
-    *backend = resolve_backend(ctx, db, n_q);
+    *backend = pick_topk(ctx, db, 0, db->v.n_refs, n_q, 1, kTopk, ~(size_t)0 >> 1).j.backend;
     return FID_OK;
 }
 
@@ -1054,7 +1155,7 @@ int fid_compare_full(fid_ctx* ctx, const fid_db* db, const uint64_t* q_dev, int3
     if (ld < db->v.n_refs) return fail(FID_EINVAL, "ld=%lld < n_refs=%lld", (long long)ld, (long long)db->v.n_refs);
     if ((reinterpret_cast<uintptr_t>(counts_dev) & 3u) != 0) return fail(FID_EINVAL, "counts pointer not 4-byte aligned");
     FID_TRY(set_device(ctx));
-    const Job j = make_job(ctx, db, n_q);
+    const Job j = make_job(ctx, db, n_q, kCounts);
     Prepared q;
     FID_TRY(prepare_queries(ctx, db, j, q_dev, n_q, mode, &q));
     return run_full(ctx, db, j, q, mode, 0, db->v.n_refs, 0, n_q, counts_dev, ld, 0, 0, true);
@@ -1109,7 +1210,7 @@ int fid_topk_range_workspace_bytes(fid_ctx* ctx, const fid_db* db, int64_t r_lo,
     if (n_q < 1 || n_q > kMaxQueries) return fail(FID_EINVAL, "n_q out of range");
     if (k < 1 || k > kMaxK) return fail(FID_EINVAL, "k=%d out of [1, %d]", k, kMaxK);
     FID_TRY(check_range(db, r_lo, r_hi));
-    *bytes = topk_layout(ctx, make_job(ctx, db, n_q), r_lo, r_hi, n_q, k).total;
+    *bytes = topk_bytes(ctx, db, r_lo, r_hi, n_q, k, false);
     return FID_OK;
 }
 
@@ -1120,7 +1221,7 @@ int fid_topk_mixed_workspace_bytes(fid_ctx* ctx, const fid_db* db, int64_t r_lo,
     if (n_q < 1 || n_q > kMaxQueries) return fail(FID_EINVAL, "n_q out of range");
     if (k < 1 || k > kMaxK) return fail(FID_EINVAL, "k=%d out of [1, %d]", k, kMaxK);
     FID_TRY(check_range(db, r_lo, r_hi));
-    *bytes = topk_layout(ctx, make_job(ctx, db, n_q, true), r_lo, r_hi, n_q, k).total;
+    *bytes = topk_bytes(ctx, db, r_lo, r_hi, n_q, k, true);
     return FID_OK;
 }
 
@@ -1159,7 +1260,7 @@ int stream_layout(const fid_ctx* ctx, int64_t n_refs, int32_t n_loci, int64_t bl
         v.v.nblk = padded_blocks(n);
         v.v.n_loci = n_loci;
         v.v.w4 = (int32_t)(rw / 2);
-        L->ws_bytes = std::max(L->ws_bytes, topk_layout(ctx, make_job(ctx, &v, n_q), 0, n, n_q, k).total);
+        L->ws_bytes = std::max(L->ws_bytes, topk_bytes(ctx, &v, 0, n, n_q, k, false));
     }
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off += align256(bytes); return o; };
@@ -1408,9 +1509,12 @@ int fid_compare_topk_noalloc(fid_ctx* ctx, const fid_db* db, const uint64_t* q_d
     if (!ctx->fixed_scratch) return fail(FID_EHIP, "fixed scratch not resolved on device %d", ctx->device);
     // the same plan, workspace layout and kernels as fid_compare_topk; the
     // staged queries and the workspace both live in the fixed array
-    const Job j = make_job(ctx, db, n_q);
-    const TopkLayout L = topk_layout(ctx, j, 0, db->v.n_refs, n_q, k);
-    const size_t qbytes = align256(query_scratch_bytes(ctx, db, n_q));
+    // (what the list scan cannot hold is refused, also where all counts would fit)
+    TopkPick pick = pick_topk(ctx, db, 0, db->v.n_refs, n_q, k, kTopkScan, kFixedScratchBytes, true);
+    if (pick.query_bytes + pick.L.total <= kFixedScratchBytes)
+        pick = pick_topk(ctx, db, 0, db->v.n_refs, n_q, k, kTopk, kFixedScratchBytes, true);
+    const TopkLayout& L = pick.L;
+    const size_t qbytes = pick.query_bytes;
     if (qbytes + L.total > kFixedScratchBytes)
         return fail(FID_ENOMEM,
                     "fid_compare_topk_noalloc: %d queries x %lld references at k=%d need %zu bytes of scratch; "
@@ -1418,7 +1522,7 @@ int fid_compare_topk_noalloc(fid_ctx* ctx, const fid_db* db, const uint64_t* q_d
                     n_q, (long long)db->v.n_refs, k, qbytes + L.total, kFixedScratchBytes);
     char* base = static_cast<char*>(ctx->fixed_scratch);
     return topk_range(ctx, db, 0, db->v.n_refs, q_dev, n_q, mode, k, base + qbytes, L.total, cnt_dev, idx_dev,
-                      nullptr, nullptr, true, base, false);
+                      nullptr, nullptr, true, base, false, &pick);
 }
 
 int fid_compare_topk_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi,
@@ -1451,7 +1555,7 @@ int fid_compare_threshold(fid_ctx* ctx, const fid_db* db, const uint64_t* q_dev,
     FID_TRY(fid_threshold_workspace_bytes(db, n_q, cap, &need));
     if (ws_bytes < need) return fail(FID_ENOMEM, "workspace %zu bytes < required %zu", ws_bytes, need);
     FID_TRY(set_device(ctx));
-    const Job j = make_job(ctx, db, n_q);
+    const Job j = make_job(ctx, db, n_q, kFiltered);
     const size_t c = (size_t)(cap > 0 ? cap : 1);
     char* ws = static_cast<char*>(ws_dev);
     unsigned long long* counter = reinterpret_cast<unsigned long long*>(ws);
@@ -1498,7 +1602,7 @@ int fid_threshold_topk_workspace_bytes(fid_ctx* ctx, const fid_db* db, int32_t n
     if (n_q < 1 || n_q > kMaxQueries) return fail(FID_EINVAL, "n_q out of range");
     if (k < 1 || k > kMaxK) return fail(FID_EINVAL, "k=%d out of [1, %d]", k, kMaxK);
     if (cap < 0) return fail(FID_EINVAL, "cap < 0");
-    *bytes = align256(topk_layout(ctx, make_job(ctx, db, n_q), 0, db->v.n_refs, n_q, k).total) + hits_bytes(cap);
+    *bytes = align256(pick_topk(ctx, db, 0, db->v.n_refs, n_q, k, kTopkScan, ~(size_t)0 >> 1).L.total) + hits_bytes(cap);
     return FID_OK;
 }
 
@@ -1514,8 +1618,10 @@ int fid_compare_threshold_topk(fid_ctx* ctx, const fid_db* db, const uint64_t* q
     if (cap > 0 && (!hidx_dev || !hcnt_dev)) return fail(FID_EINVAL, "NULL hit output buffer");
     if (cap < 0) return fail(FID_EINVAL, "cap < 0");
     if (!aligned16(ws_dev)) return fail(FID_EINVAL, "workspace not 16-byte aligned");
-    const Job j = make_job(ctx, db, n_q);
-    const TopkLayout L = topk_layout(ctx, j, 0, db->v.n_refs, n_q, k);
+    const size_t avail = ws_bytes > hits_bytes(cap) ? (ws_bytes - hits_bytes(cap)) & ~(size_t)255 : 0;
+    const TopkPick pick = pick_topk(ctx, db, 0, db->v.n_refs, n_q, k, kTopkScan, avail);
+    const Job& j = pick.j;
+    const TopkLayout& L = pick.L;
     const size_t tk_bytes = align256(L.total);
     if (ws_bytes < tk_bytes + hits_bytes(cap))
         return fail(FID_ENOMEM, "workspace %zu bytes < required %zu", ws_bytes, tk_bytes + hits_bytes(cap));
@@ -1524,7 +1630,7 @@ int fid_compare_threshold_topk(fid_ctx* ctx, const fid_db* db, const uint64_t* q
     if (j.backend != FID_BACKEND_MFMA_FP4 || L.direct) {
         // two scans; the top-k first, so that its output is complete whatever
         // the threshold call returns
-        FID_TRY(topk_range(ctx, db, 0, db->v.n_refs, q_dev, n_q, mode, k, ws, L.total, cnt_dev, idx_dev));
+        FID_TRY(topk_range(ctx, db, 0, db->v.n_refs, q_dev, n_q, mode, k, ws, avail, cnt_dev, idx_dev));
         return fid_compare_threshold(ctx, db, q_dev, n_q, mode, thr_dev, hw, hits_bytes(cap), cap, offs_dev,
                                      hidx_dev, hcnt_dev, total_host);
     }
@@ -1661,7 +1767,7 @@ int fid_compare_threshold_streamed(fid_ctx* ctx, const uint64_t* rows_host, int6
         hip(hipEventRecord(freed[slot], ctx->stream), "hipEventRecord");
         if (!st && b == 0) {
             // every block has the same row length: one query preparation
-            j = make_job(ctx, db, n_q);
+            j = make_job(ctx, db, n_q, kFiltered);
             st = prepare_queries(ctx, db, j, q_dev, n_q, mode, &q);
         }
         if (!st) {

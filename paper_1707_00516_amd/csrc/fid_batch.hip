@@ -436,7 +436,7 @@ int plan_batch(const fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
         // bound items with the compute-bound ones.  A backend forced on the
         // context decides instead: int8 jobs run as per-call top-k inside
         // the batch, popcount jobs share the persistent popcount launch.
-        if (auto_family(ctx, J.db, std::max(J.n_q, fp4_queries_per_wg())) == FID_BACKEND_MFMA_FP4) {
+        if (auto_family(ctx, J.db) == FID_BACKEND_MFMA_FP4) {
             BatchPlan::F4 f{};
             f.job = j;
             f.n_q = J.n_q;

@@ -62,8 +62,11 @@ int thresh_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, con
 int64_t seed_prefix(int64_t n_refs, int backend, int32_t n_q);
 // Grow the context's scratch to hold `bytes` of staged queries (may allocate).
 int scratch_reserve(fid_ctx* ctx, size_t bytes);
-// The kernel family (fid_backend) a call with n_q queries on db resolves to.
-int auto_family(const fid_ctx* ctx, const fid_db* db, int32_t n_q);
+// Workspace of a list scan over db with one mode or per-query modes: of the
+// family that is fastest, or the least with which the call is accepted.
+size_t topk_scan_bytes(const fid_ctx* ctx, const fid_db* db, int32_t n_q, int32_t k, bool least);
+// The kernel family (fid_backend) a call of full query tiles on db resolves to.
+int auto_family(const fid_ctx* ctx, const fid_db* db);
 bool batch_routes_to_matrix_cores(const fid_ctx* ctx, const fid_db* db, int32_t n_q);
 // Scratch bytes the query preparation of such a call needs.
 size_t query_scratch_bytes(const fid_ctx* ctx, const fid_db* db, int32_t n_q);

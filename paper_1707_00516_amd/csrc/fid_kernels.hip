@@ -212,11 +212,12 @@ hipError_t launch_db_build(const uint64_t* rows, int64_t n_refs, int32_t row_wor
 // Packed query rows -> [n_q][qw] 32-bit words, loci >= L cleared, zero padded
 // to the scan's chunk width.  Mixture queries are stored inverted so that
 // Eq. 1 becomes a plain AND: (R ^ Q) & R == R & ~Q.
+template <bool CLEAR>
 __global__ void stage_kernel(const uint64_t* __restrict__ q, int32_t n_q, int32_t row_words,
                              int32_t n_loci, int mode, const int32_t* __restrict__ qmode,
                              uint32_t* __restrict__ out, int32_t qw, uint64_t* __restrict__ clear)
 {
-    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0ull;
+    if (CLEAR && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0ull;
     const int64_t total = (int64_t)n_q * qw;
     const int32_t l32 = (n_loci + 31) / 32;
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
@@ -241,8 +242,8 @@ hipError_t launch_stage_queries(const uint64_t* q, int32_t n_q, int32_t row_word
     int64_t blocks = (total + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(stage_kernel, dim3((unsigned)blocks), dim3(256), 0, s, q, n_q, row_words,
-                       n_loci, mode, qmode, out, qw, clear);
+    hipLaunchKernelGGL(clear ? stage_kernel<true> : stage_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, q,
+                       n_q, row_words, n_loci, mode, qmode, out, qw, clear);
     return hipGetLastError();
 }
 

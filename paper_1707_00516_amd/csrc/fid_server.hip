@@ -492,36 +492,38 @@ int fid_server_create(fid_ctx* ctx, const fid_db* db, const fid_server_config* c
     s->ctx->backend = ctx->backend;
     // workspace: the largest top-k any tick may run -- a range of up to the
     // whole database, with one mode or per-query modes
-    auto ws_for = [&](int32_t n, size_t* bytes) -> int {
+    bool least = false;  // slots before the faster kernels' larger lists
+    auto ws_for = [&](int32_t n) -> size_t {
         size_t best = 0;
         for (int32_t m = 1; m <= n; m = m < 64 ? m + 1 : m + 64) {  // the family (and layout) depends on m
-            size_t a = 0, b = 0;
-            FID_TRY(fid_topk_workspace_bytes(s->ctx, db, m, cfg->k, &a));
-            FID_TRY(fid_topk_mixed_workspace_bytes(s->ctx, db, 0, db->v.n_refs, m, cfg->k, &b));
-            best = std::max(best, std::max(a, b));
+            best = std::max(best, topk_scan_bytes(s->ctx, db, m, cfg->k, least));
             if (m == n) break;
             if (m >= 64 && m + 64 > n) m = n - 64;
         }
-        *bytes = best;
-        return FID_OK;
+        return best;
     };
     auto total_for = [&](int32_t n, size_t w) {
         return server_bytes(n, s->rw, cfg->k, w, (int64_t)n * s->cfg.hits_per_query);
     };
-    int32_t lo = 0, hi = cfg->max_queries;
-    size_t ws = 0;
-    while (lo < hi) {  // largest slot count whose state + workspace fit the budget
-        const int32_t mid = lo + (hi - lo + 1) / 2;
-        size_t w = 0;
-        st = ws_for(mid, &w);
-        if (st) return cleanup(st);
-        if (total_for(mid, w) <= cfg->hbm_budget) lo = mid;
-        else hi = mid - 1;
+    auto slots = [&]() {  // largest slot count whose state + workspace fit the budget
+        int32_t lo = 0, hi = cfg->max_queries;
+        while (lo < hi) {
+            const int32_t mid = lo + (hi - lo + 1) / 2;
+            if (total_for(mid, ws_for(mid)) <= cfg->hbm_budget) lo = mid;
+            else hi = mid - 1;
+        }
+        return lo;
+    };
+    int32_t lo = slots();
+    if (lo < cfg->max_queries) {
+        least = true;
+        const int32_t n = slots();
+        least = n > lo;
+        lo = std::max(lo, n);
     }
     if (lo < 1) return cleanup(fail(FID_EBUDGET, "hbm_budget %zu holds no query slot", cfg->hbm_budget));
     s->max_slots = lo;
-    st = ws_for(lo, &ws);
-    if (st) return cleanup(st);
+    const size_t ws = ws_for(lo);
     s->ws_bytes = ws;
     s->hcap = (int64_t)lo * s->cfg.hits_per_query;
     s->device_bytes = total_for(lo, ws);
