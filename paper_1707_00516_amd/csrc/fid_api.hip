@@ -560,6 +560,20 @@ int64_t seed_refs(int64_t n_refs, int backend, int32_t n_q)
     return s < n_refs ? s : n_refs;
 }
 
+// A call by itself, of rows short enough for the seed to be cheap, takes a
+// longer prefix: the first bound decides how many candidates each wave meets
+// before it learns of the others' (a wave of a scan of 2M references has 8-30
+// tiles).  Up to 1/16 of the references (1/32 at 2048 loci) and 16M counts, as
+// measured (300 loci x 2M: 128 queries 204 us at 1/128, 144 at 1/16; 512
+// queries 343 at 1/128, 320 at 1/64, 358 at 1/16; 2048 loci x 4M, 128 queries:
+// 392 at 1/128, 378 at 1/32, 398 at 1/16).
+int64_t long_seed_refs(int64_t n_refs, int32_t n_q, int32_t n_loci)
+{
+    int64_t s = std::min<int64_t>(n_refs / (16 * std::max(1, n_loci / 1024)), 131072);
+    s = std::min<int64_t>(s, ((int64_t)16 << 20) / n_q) / 64 * 64;
+    return std::max(s, seed_refs(n_refs, FID_BACKEND_MFMA_FP4, n_q));
+}
+
 struct TopkLayout {
     bool direct;          // whole count block fits: count then select
     Plan plan;
@@ -567,13 +581,14 @@ struct TopkLayout {
     size_t off_lists, off_fills, off_counts, off_thr, off_level, off_wit, total;
 };
 
-// direct: the whole range's counts, then the selection (else the list scan).
+// seed == r_hi - r_lo: the whole range's counts, then the selection (else the
+// list scan).
 TopkLayout topk_layout(const fid_ctx* ctx, const Job& j, int64_t r_lo, int64_t r_hi, int32_t n_q,
-                       int32_t k, bool direct)
+                       int32_t k, int64_t seed)
 {
     TopkLayout L{};
     const int64_t n = r_hi - r_lo;
-    L.seed = direct ? n : seed_refs(n, j.backend, n_q);
+    L.seed = seed;
     L.direct = L.seed == n;
     size_t off = 0;
     if (L.direct) {
@@ -615,7 +630,8 @@ bool direct_pays(int backend, int64_t n, int32_t n_q)
 }
 
 // A top-k call's family and layout: what is fastest of what fits.  A workspace
-// too small for all counts holds the lists, and one that was sized for the
+// too small for all counts holds the lists, with a seed as long as it has
+// room for, and one that was sized for the
 // popcount scan (a call with another number of queries) still serves it, so
 // that a workspace kept for several calls is not refused.
 struct TopkPick {
@@ -648,20 +664,21 @@ TopkPick pick_topk(const fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r
                             !scan && direct_pays(FID_BACKEND_MFMA_FP4, n, n_q) ? kCounts : kFiltered);
     if (per_query && b == FID_BACKEND_MFMA) b = FID_BACKEND_POPCOUNT;
     TopkPick p{}, first{};
-    auto fits = [&](int backend, bool direct) {
+    auto fits = [&](int backend, int64_t seed) {
         p.j = job_of(db, backend);
-        p.L = topk_layout(ctx, p.j, r_lo, r_hi, n_q, k, direct);
+        p.L = topk_layout(ctx, p.j, r_lo, r_hi, n_q, k, seed);
         p.query_bytes = align256(query_bytes_of(p.j, n_q));
         return p.L.total + (with_queries ? p.query_bytes : 0) <= avail;
     };
-    if (!scan && direct_pays(b, n, n_q) && fits(b, true)) return p;
-    if (fits(b, false)) return p;
+    if (!scan && direct_pays(b, n, n_q) && fits(b, n)) return p;
+    if (b == FID_BACKEND_MFMA_FP4 && fits(b, long_seed_refs(n, n_q, db->v.n_loci))) return p;
+    if (fits(b, seed_refs(n, b, n_q))) return p;
     first = p;
     if (b == FID_BACKEND_MFMA_FP4 && forced_backend(ctx, db) == FID_BACKEND_AUTO &&
-        fits(FID_BACKEND_POPCOUNT, false))
+        fits(FID_BACKEND_POPCOUNT, seed_refs(n, FID_BACKEND_POPCOUNT, n_q)))
         return p;
     // a workspace sized by a call without a bound
-    if (scan && !with_queries && direct_pays(b, n, n_q) && fits(b, true)) return p;
+    if (scan && !with_queries && direct_pays(b, n, n_q) && fits(b, n)) return p;
     return first;
 }
 
@@ -848,7 +865,11 @@ size_t topk_scan_bytes(const fid_ctx* ctx, const fid_db* db, int32_t n_q, int32_
     for (const TopkUse use : {kTopkScan, kTopkPerQueryScan}) {
         const size_t any = ~(size_t)0 >> 1;
         size_t b = pick_topk(ctx, db, 0, db->v.n_refs, n_q, k, use, any).L.total;
-        if (least) b = std::min(b, pick_topk(ctx, db, 0, db->v.n_refs, n_q, k, use, b - 1).L.total);
+        while (least) {
+            const size_t c = pick_topk(ctx, db, 0, db->v.n_refs, n_q, k, use, b - 1).L.total;
+            if (c >= b) break;
+            b = c;
+        }
         best = std::max(best, b);
     }
     return best;

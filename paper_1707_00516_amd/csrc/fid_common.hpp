@@ -97,7 +97,7 @@ struct MfmaBuffers {
     uint32_t* fills;
     const uint32_t* thr_init;
     const uint32_t* level;     // top-k witness levels, [q][kWitLevels] (optional)
-    uint32_t* wit;             // witnesses counted below each, [q][kWitLevels]
+    uint32_t* wit;             // witnesses counted below each and not below the next, [q][kWitLevels]
     const int32_t* thr;
     unsigned long long* hit_count;
     uint64_t* hit_keys;

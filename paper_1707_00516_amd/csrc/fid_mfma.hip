@@ -144,11 +144,12 @@ constexpr int kCandQ4 = 64;
 // Drain the queue of n <= 64 entries into the wave's top-k lists.  Every lane
 // takes one entry, so the bound, fill and witness lookups of all candidates
 // happen at once.  The entries of one query below its bound are appended at
-// the next free slots; a list that fills takes its entries one by one, since
-// its new bound needs the list's worst key.  Witness counts (every queued
-// candidate below a level: each is a distinct reference of its query, as the
-// scan meets a pair once) go to the workgroup's LDS counters wloc, which the
-// waves add to the global ones every few tiles.  Inlined where nothing of the
+// the next free slots, all queries at once; a list that fills takes its entries
+// one by one, since its new bound needs the list's worst key.  Witness counts
+// (every queued candidate, under the lowest level that it is below: each is a
+// distinct reference of its query, as the scan meets a pair once) go to the
+// workgroup's LDS counters wloc, which the waves add to the global ones now
+// and then.  Inlined where nothing of the
 // tile but the candidate test's operands is live: an out-of-line call waits
 // for every memory operation of the wave on entry and on return, the next
 // tile's prefetch and its own list stores included.
@@ -165,12 +166,31 @@ __device__ __forceinline__ void fp4_drain_lists(const lds_u32* cq, int n, int64_
     const uint32_t t0 = act ? lthr[m] : 0u;
     const uint32_t f0 = act ? lfill[m] : 0u;
     if (wloc && act) {
+        // the levels fall, so the count is below the first `under` of them;
+        // the lowest of these is worth a count while it would lower the bound
+        int under = 0;
+        uint32_t lowest = t0;
 #pragma unroll
-        for (int l = 0; l < kWitLevels; ++l)
-            if (c < tlvl[kWitLevels * m + l])
-                __hip_atomic_fetch_add(wloc + kWitLevels * m + l, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        for (int l = 0; l < kWitLevels; ++l) {
+            const uint32_t level = tlvl[kWitLevels * m + l];
+            under += c < level;
+            lowest = c < level ? level : lowest;
+        }
+        if (lowest < t0)
+            __hip_atomic_fetch_add(wloc + kWitLevels * m + under - 1, 1u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     const bool keep = act && c < t0;
+    // no list can fill up: every entry takes its query's next slot
+    if (!__builtin_amdgcn_ballot_w64(keep && f0 + (uint32_t)n >= (uint32_t)k)) {
+        if (keep) {
+            const uint32_t slot =
+                __hip_atomic_fetch_add(lfill + m, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            lists[(int64_t)m * qstride + slot] = key;
+        }
+        wave_lds_sync();
+        return;
+    }
     uint64_t rem = __builtin_amdgcn_ballot_w64(keep);
     while (rem) {
         const int lead = __builtin_ctzll(rem);
@@ -880,6 +900,8 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
 #pragma unroll
     for (int a = 0; a < kRing4; ++a) ring[a] = lds_a(x_first, 0, a);
     v4f acc[NA][kNB4];
+    int refresh = 0;               // the tile at which the bounds are renewed
+    const int gap = min(max(w.n_slots >> 6, 1), 4);
     for (int it = 0; it < nt; ++it, toff += tile_bytes) {
         const int64_t tile = tb + it;
         const int64_t rbase = base + tile * kRefsPerWG4 + (int64_t)wv * kRefsPerWave4;
@@ -887,11 +909,16 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
         if (it + 1 < nt)
             dma4(pcst + (uint32_t)(~it & 1) * (kRefsPerWave4 * 4), wpc + (int64_t)(it + 1) * kRefsPerWG4,
                  (uint32_t)lane * 4u);
-        // every 4th tile: the query tile's witness counts, read by the
+        // now and then the query tile's witness counts, read by the
         // epilogue; the workgroup's waves share them, each staging an eighth
         // (any value read is a count some time during the scan, and counts
-        // only grow; rows past the tile's queries repeat its last query)
-        if (witness && (it & 3) == 0) {
+        // only grow; rows past the tile's queries repeat its last query).
+        // The k-th smallest count falls with the share of the database seen, so
+        // the renewals thin out: after each quarter more tiles, at most 16
+        // apart, and at least a tile per 64 workgroups that count into the same
+        // few lines of memory (64 queries x 2M x 300 loci, 256 workgroups: 248
+        // us with a renewal each tile, 130 with one every fourth).
+        if (witness && it == refresh) {
             constexpr int kPer = kWitLevels * kQB4 / kWavesM;
 #pragma unroll
             for (int h = 0; h < (kPer + 63) / 64; ++h) {
@@ -1058,7 +1085,13 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
             // fit is to be spilled around the selection, never in the scan loop)
             if (__builtin_expect_with_probability(__builtin_amdgcn_ballot_w64(any) != 0, 0, 0.99999)) {
                 // Queue the candidates of each block that holds one and drain
-                // the queue.  Should it fill up, the elements from `resume` on
+                // the queue.  A third of the tiles of a short row's scan come
+                // here, so few operations matter: a block with a candidate,
+                // then four elements with one, then the element, each a test
+                // that the whole wave takes alike (512 queries x 10M x 512
+                // loci, cycles a visit: 7400 with a test per element, 2600 so;
+                // draining its 3.3 candidates 2600 list by list, 1200 with all
+                // appended at once; the call 1250 us and 990).  Should it fill up, the elements from `resume` on
                 // are queued in another pass (an element has at most 64
                 // candidates, one per lane, so every pass gets on); their
                 // bounds have tightened meanwhile, which the drain looks up.
@@ -1085,10 +1118,15 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
                         const int32_t pq = tpcq[m];
 #pragma unroll
                         for (int j = 0; j < kNB4; ++j) {
+                            float x0 = acc[a][j][0];
+                            __asm__ volatile("" : "+v"(x0));  // (not computed ahead for all blocks)
+                            const float top4 = fmaxf(fmaxf(fmaxf(x0, acc[a][j][1]), acc[a][j][2]), acc[a][j][3]);
+                            if (!__builtin_amdgcn_ballot_w64(top4 > ca)) continue;
 #pragma unroll
                             for (int i = 0; i < 4; ++i) {
                                 const int e = 16 * a + 4 * j + i;
                                 const float x = acc[a][j][i];
+                                if (!__builtin_amdgcn_ballot_w64(x > ca)) continue;
                                 const int ref = 16 * j + i + row0;
                                 const bool cand = x > ca && (uint32_t)(ref - in_lo) < in_n;
                                 const uint64_t cm = __builtin_amdgcn_ballot_w64(cand);
@@ -1123,18 +1161,21 @@ __device__ __forceinline__ void fp4_work(const Fp4Work& w)
                     resume = stop;
                 } while (resume < 16 * NA);
             }
-            if (witness && (it & 3) == 0) {
+            if (witness && it == refresh) {
+                refresh += min(max(it >> 2, gap), 16);
                 fp4_flush_witness(wloc, wit + kWitLevels * q0, kWitLevels * nq_tile, wv, lane_e);
                 // k distinct references below one of a query's witness
-                // levels make that level a bound
+                // levels make that level a bound (a counter holds those below
+                // its level but not below the next lower one)
 #pragma unroll
                 for (int h = 0; h < kQB4 / 64; ++h) {
                     const int i = lane_e + 64 * h;
-                    uint32_t b = lthr[i];
+                    uint32_t b = lthr[i], below = 0;
 #pragma unroll
-                    for (int l = 0; l < kWitLevels; ++l)
-                        if (wst[kWitLevels * i + l] >= (uint32_t)w.k && tlvl[kWitLevels * i + l] < b)
-                            b = tlvl[kWitLevels * i + l];
+                    for (int l = kWitLevels - 1; l >= 0; --l) {
+                        below += wst[kWitLevels * i + l];
+                        if (below >= (uint32_t)w.k) b = min(b, tlvl[kWitLevels * i + l]);
+                    }
                     lthr[i] = b;
                 }
                 wave_lds_sync();

@@ -29,7 +29,7 @@ def ctx():
     (16384, 300, 256), (16385, 300, 255), (32768, 1024, 256), (32769, 1024, 11), (32769, 1024, 12), (49152, 300, 32),
     (49153, 300, 32), (131072, 64, 3), (131073, 64, 3), (131072, 64, 127), (262144, 64, 200), (262144, 64, 201),
     (262145, 64, 200), (262144, 2048, 5), (262144, 2048, 6), (262145, 2048, 11), (262145, 2048, 12), (33000, 5000, 2),
-    (33000, 5000, 1)])
+    (33000, 5000, 1), (540_000, 300, 64), (400_001, 1000, 150), (1_200_000, 100, 17)])
 def test_routes_agree(ctx, n, L, n_q, k=5):
     from paper_1707_00516_amd import (FID_BACKEND_AUTO, FID_BACKEND_POPCOUNT, FID_ENOMEM, FidError,
                                       fid_compare_topk, fid_compare_topk_bounded, fid_compare_topk_noalloc,
