@@ -682,6 +682,11 @@ TopkPick pick_topk(const fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r
     return first;
 }
 
+TopkUse topk_use(bool per_query, bool bounded)
+{
+    return per_query ? (bounded ? kTopkPerQueryScan : kTopkPerQuery) : (bounded ? kTopkScan : kTopk);
+}
+
 // Workspace bytes with which a call of this use takes its fastest path, with
 // or without a bound.
 size_t topk_bytes(const fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, int32_t n_q, int32_t k,
@@ -760,11 +765,13 @@ int check_modes_dev(fid_ctx* ctx, const int32_t* modes_dev, int32_t n_q)
 // bound_dev (optional, device [n_q]): a caller-known exclusive bound per query
 // ("count < bound" loses nothing); with seed = false it replaces the seed
 // pass, with seed = true the tighter of the two filters.  qarea: where the
-// staged queries of `given`, the caller's pick, go.
+// staged queries of `given`, the caller's pick, go.  hits: threshold hits of the
+// same scan (only where topk_scan_takes_hits()).
 int topk_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const uint64_t* q_dev,
                int32_t n_q, int mode, int32_t k, void* ws_dev, size_t ws_bytes, int32_t* cnt_dev,
                int64_t* idx_dev, const int32_t* qmode = nullptr, const uint32_t* bound_dev = nullptr,
-               bool seed = true, char* qarea = nullptr, bool timed = true, const TopkPick* given = nullptr)
+               bool seed = true, char* qarea = nullptr, bool timed = true, const TopkPick* given = nullptr,
+               const HitSink* hits = nullptr)
 {
     const bool per_query = mode == kModePerQuery;
     FID_TRY(check_common(ctx, db, q_dev, n_q, per_query ? FID_MODE_MIXTURE : mode));
@@ -773,11 +780,13 @@ int topk_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const
     if (k < 1 || k > kMaxK) return fail(FID_EINVAL, "k=%d out of [1, %d]", k, kMaxK);
     if (!cnt_dev || !idx_dev || !ws_dev) return fail(FID_EINVAL, "NULL buffer");
     if (!aligned16(ws_dev)) return fail(FID_EINVAL, "workspace not 16-byte aligned");
-    const TopkUse use = per_query ? (bound_dev ? kTopkPerQueryScan : kTopkPerQuery) : (bound_dev ? kTopkScan : kTopk);
-    const TopkPick pick = given ? *given : pick_topk(ctx, db, r_lo, r_hi, n_q, k, use, ws_bytes);
+    const TopkPick pick =
+        given ? *given : pick_topk(ctx, db, r_lo, r_hi, n_q, k, topk_use(per_query, bound_dev), ws_bytes);
     const Job& j = pick.j;
     const TopkLayout& L = pick.L;
     if (ws_bytes < L.total) return fail(FID_ENOMEM, "workspace %zu bytes < required %zu", ws_bytes, L.total);
+    if (hits && (j.backend != FID_BACKEND_MFMA_FP4 || L.direct))
+        return fail(FID_EINVAL, "this top-k's scan takes no threshold hits");
     FID_TRY(set_device(ctx));
     Prepared q;
     FID_TRY(prepare_queries(ctx, db, j, q_dev, n_q, mode, &q, qmode, qarea));
@@ -814,7 +823,14 @@ int topk_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const
     o.thr_init = thr_init;
     o.level = level;
     o.wit = wit;
-    FID_TRY(run_scan(ctx, j, mode, EPI_TOPK, p, q, o, timed));
+    if (hits) {
+        p.hit_cap = hits->cap;
+        o.thr = hits->thr;
+        o.hit_count = hits->counter;
+        o.hit_keys = hits->keys;
+        o.hit_cnt = hits->vals;
+    }
+    FID_TRY(run_scan(ctx, j, mode, hits ? EPI_BOTH : EPI_TOPK, p, q, o, timed));
     FID_HIP(launch_merge_lists(lists, fills, n_q, L.plan.list_workers, k, db->v.n_loci, cnt_dev, idx_dev,
                                ctx->stream),
             "merge launch");
@@ -825,12 +841,19 @@ int topk_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const
 
 namespace fid {
 
-int topk_range_bounded(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const uint64_t* q_dev,
-                       const int32_t* modes_dev, int32_t n_q, int32_t k, void* ws_dev, size_t ws_bytes,
-                       int32_t* cnt_dev, int64_t* idx_dev, const uint32_t* bound_dev, bool seed)
+bool topk_scan_takes_hits(const fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, int32_t n_q, int32_t k,
+                          bool per_query, bool bounded, size_t ws_bytes)
 {
-    return topk_range(ctx, db, r_lo, r_hi, q_dev, n_q, kModePerQuery, k, ws_dev, ws_bytes, cnt_dev, idx_dev,
-                      modes_dev, bound_dev, seed);
+    const TopkPick p = pick_topk(ctx, db, r_lo, r_hi, n_q, k, topk_use(per_query, bounded), ws_bytes);
+    return p.j.backend == FID_BACKEND_MFMA_FP4 && !p.L.direct;
+}
+
+int topk_range_hits(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const uint64_t* q_dev, int mode,
+                    const int32_t* modes_dev, int32_t n_q, int32_t k, void* ws_dev, size_t ws_bytes,
+                    int32_t* cnt_dev, int64_t* idx_dev, const uint32_t* bound_dev, bool seed, const HitSink* hits)
+{
+    return topk_range(ctx, db, r_lo, r_hi, q_dev, n_q, modes_dev ? kModePerQuery : mode, k, ws_dev, ws_bytes, cnt_dev,
+                      idx_dev, modes_dev, bound_dev, seed, nullptr, true, nullptr, hits);
 }
 
 int thresh_range(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const uint64_t* q_dev, int32_t n_q,

@@ -45,12 +45,25 @@ int set_device(const fid_ctx* ctx);
 // return the end event to record after it (else *end = nullptr).
 int timing_begin(fid_ctx* ctx, hipStream_t s, hipEvent_t* end);
 
-// fid_compare_topk_mixed with a caller-known exclusive bound per query
-// (bound_dev, device [n_q]); seed = false skips the seed pass and filters
-// with the bound alone, seed = true takes the tighter of the two.
-int topk_range_bounded(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const uint64_t* q_dev,
-                       const int32_t* modes_dev, int32_t n_q, int32_t k, void* ws_dev, size_t ws_bytes,
-                       int32_t* cnt_dev, int64_t* idx_dev, const uint32_t* bound_dev, bool seed);
+// Where a scan appends threshold hits ("count <= thr[q]", -1: none of the query's),
+// as thresh_range() does.
+struct HitSink {
+    const int32_t* thr;
+    unsigned long long* counter;
+    uint64_t* keys;
+    int32_t* vals;
+    int64_t cap;
+};
+// Top-k of one mode (modes_dev NULL) or per-query modes, optionally with a
+// caller-known exclusive bound per query (bound_dev, device [n_q]; seed = false
+// skips the seed pass and filters with the bound alone, seed = true takes the
+// tighter of the two), and optionally with the threshold hits of the same
+// scan, where topk_scan_takes_hits() says that it is one.
+bool topk_scan_takes_hits(const fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, int32_t n_q, int32_t k,
+                          bool per_query, bool bounded, size_t ws_bytes);
+int topk_range_hits(fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r_hi, const uint64_t* q_dev, int mode,
+                    const int32_t* modes_dev, int32_t n_q, int32_t k, void* ws_dev, size_t ws_bytes,
+                    int32_t* cnt_dev, int64_t* idx_dev, const uint32_t* bound_dev, bool seed, const HitSink* hits);
 // Threshold hits of queries x references [r_lo, r_hi) appended to (keys,
 // vals) with the shared counter (keys q << 40 | r, q the query's index in
 // q_dev; hits past cap are counted, not stored).  No sort, no sync.

@@ -162,7 +162,7 @@ namespace {
 
 // tables of one tick: [0] fresh slots, [1] in-flight slots (gathered order),
 // [2] their modes, [3] finishing slots, [4] threshold queries (gathered
-// index, mixture ones first), [5] their thresholds
+// index; mixture ones first, or all in flight), [5] their thresholds
 constexpr int kTables = 6;
 constexpr int32_t kDefaultHitsPerQuery = 256;
 
@@ -199,8 +199,25 @@ int run_tick(fid_server* s, const std::vector<Request*>& act, const std::vector<
     }
     for (Request* r : fresh)
         for (int32_t sl : r->slots) hs[n_fresh++] = sl;
-    // threshold queries: mixture ones first, then identity ones
-    for (int pass = 0; pass < 2; ++pass) {
+    // Threshold hits come from the top-k's own scan where that is a list scan on
+    // the matrix cores (8 requests of 1-48 queries x 20M x 2048 loci, half with
+    // thresholds: 12.6 ms with a scan per mode after it, 11.4 so): table 5 is then
+    // every query's threshold, -1 without one.  Else a scan per mode follows,
+    // of the threshold queries: mixture ones first, then identity ones.
+    bool any_thr = false;
+    for (Request* r : act) any_thr = any_thr || !r->thr.empty();
+    const bool fused = any_thr && topk_scan_takes_hits(s->ctx, s->db, r_lo, r_hi, n_act, k, !(whole && one_mode),
+                                                       !whole, s->ws_bytes);
+    if (fused) {
+        int32_t g = 0;
+        for (Request* r : act)
+            for (int32_t q = 0; q < r->r.n_q; ++q, ++g) {
+                hs[4 * M + g] = g;
+                hs[5 * M + g] = r->thr.empty() ? -1 : r->thr[q];
+            }
+        n_thr = n_act;
+    }
+    for (int pass = 0; pass < 2 && !fused; ++pass) {
         int32_t g = 0;
         for (Request* r : act) {
             const bool want = r->r.mode == (pass == 0 ? FID_MODE_MIXTURE : FID_MODE_IDENTITY);
@@ -246,20 +263,20 @@ int run_tick(fid_server* s, const std::vector<Request*>& act, const std::vector<
     }
 
     // top-k of every query in flight over the tick's references
-    if (whole && one_mode) {
-        FID_TRY(fid_compare_topk_range(s->ctx, s->db, r_lo, r_hi, qsrc, n_act, act[0]->r.mode, k, s->ws,
-                                       s->ws_bytes, s->tcnt, s->tidx));
-    } else if (whole) {
-        FID_TRY(topk_range_bounded(s->ctx, s->db, r_lo, r_hi, qsrc, modes, n_act, k, s->ws, s->ws_bytes, s->tcnt,
-                                   s->tidx, nullptr, true));
+    const HitSink sink{s->dslots + 5 * (size_t)M, s->hcounter, s->hkeys, s->hvals, s->hcap};
+    if (n_thr)
+        FID_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(s->hcounter), 4, 0ull, s->stream), "fill launch");
+    if (whole) {
+        FID_TRY(topk_range_hits(s->ctx, s->db, r_lo, r_hi, qsrc, act[0]->r.mode, one_mode ? nullptr : modes, n_act, k,
+                                s->ws, s->ws_bytes, s->tcnt, s->tidx, nullptr, true, fused ? &sink : nullptr));
     } else {
         // queries past their first chunk are filtered by their running k-th
         // count; only a tick that admits new queries pays the seed pass
         hipLaunchKernelGGL(gather_u32_kernel, dim3((unsigned)((n_act + 255) / 256)), dim3(256), 0, s->stream,
                            s->bound, tbl, n_act, s->tbound);
         FID_HIP(hipGetLastError(), "gather launch");
-        FID_TRY(topk_range_bounded(s->ctx, s->db, r_lo, r_hi, qsrc, modes, n_act, k, s->ws, s->ws_bytes, s->tcnt,
-                                   s->tidx, s->tbound, n_fresh > 0));
+        FID_TRY(topk_range_hits(s->ctx, s->db, r_lo, r_hi, qsrc, FID_MODE_MIXTURE, modes, n_act, k, s->ws, s->ws_bytes,
+                                s->tcnt, s->tidx, s->tbound, n_fresh > 0, fused ? &sink : nullptr));
         FID_HIP(launch_fold_topk(s->tcnt, s->tidx, tbl, n_act, k, 0, s->running, s->bound, s->stream),
                 "fold launch");
         if (n_fin)
@@ -275,10 +292,9 @@ int run_tick(fid_server* s, const std::vector<Request*>& act, const std::vector<
     }
 
     // threshold hits of the tick's references: one scan per mode
-    if (n_thr) {
+    if (n_thr && !fused) {
         unsigned long long* counter = s->hcounter;
         int64_t* ends = reinterpret_cast<int64_t*>(s->hcounter + 1);
-        FID_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(s->hcounter), 4, 0ull, s->stream), "fill launch");
         hipLaunchKernelGGL(gather_rows_kernel, dim3(grid_for((int64_t)n_thr * s->rw)), dim3(256), 0, s->stream, qsrc,
                            s->dslots + 4 * (size_t)M, n_thr, s->rw, s->trows);
         FID_HIP(hipGetLastError(), "gather launch");
@@ -295,9 +311,10 @@ int run_tick(fid_server* s, const std::vector<Request*>& act, const std::vector<
             FID_HIP(launch_offset_block_hits(counter, ends, n_mix ? 1 : 0, s->hkeys, s->hcap, (int64_t)n_mix << kIdxBits,
                                              s->stream), "hit offsets");
         }
-        FID_HIP(hipMemcpyAsync(s->hcount_host, counter, sizeof(unsigned long long), hipMemcpyDeviceToHost, s->stream),
-                "hit count copy");
     }
+    if (n_thr)
+        FID_HIP(hipMemcpyAsync(s->hcount_host, s->hcounter, sizeof(unsigned long long), hipMemcpyDeviceToHost,
+                               s->stream), "hit count copy");
     FID_HIP(hipStreamSynchronize(s->stream), "hipStreamSynchronize");
 
     if (n_thr) {
