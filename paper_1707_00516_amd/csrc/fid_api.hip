@@ -214,6 +214,7 @@ int refs_per_lane(int nw, bool chunked)
 struct Plan {
     int32_t n_rsplit;            // popcount: waves along references; MFMA: workgroups
     int32_t q_per_worker;
+    int32_t n_qtiles;            // fp4: query tiles
     int32_t n_workers;           // popcount: waves; MFMA: workgroups
     int32_t lds_words_per_wave;
     int32_t list_workers;        // top-k list owners along references
@@ -302,11 +303,13 @@ enum Reduce { kCounts, kFiltered };
 // 400k-5M references): 50, 28, 10 and 6 at 300, 1024, 2048 and 8192 loci.
 // 12288 / loci and twice that follow them (2048 loci x 400k references, top-32:
 // 32 queries 113 us popcount, 75 fp4; 4 queries 49 and 59).
-// A database of few 128-reference tiles leaves workgroups without one, and the
-// popcount scan splits finer (all counts; us popcount, fp4): 5000 x 2048 loci,
-// 256 queries 13.7, 19.2; 10k x 2048, 128 queries 13.3, 19.1; 20k x 1024, 64
-// queries 9.3, 11.6, 256 19.3, 18.2; 20k x 2048, 8 queries 9.1, 8.6; 40k x 512,
-// 128 queries 13.8, 17.4; 40k x 1024, 32 queries 9.2, 9.1.
+// Up to 65536 references a call of few counts is launches and latency: about
+// 8 us popcount, and 8 to 30 us fp4 (a chain of 1024-locus halves per tile), so
+// it takes some work for fp4 to lead (all counts; us popcount, fp4): 5000 x 1024
+// loci, 256 queries 9.2, 8.3, 128 7.8, 8.2; 10k x 2048, 64 queries 9.8, 9.3, 32
+// 8.5, 9.0; 20k x 2048, 16 queries 11.2, 9.0; 40k x 512, 64 queries 9.7, 9.6;
+// 10k x 8192, 16 queries 19.4, 18.5; 5000 x 8192, 32 queries 16.4, 18.4, 64 21.0,
+// 18.7; 5000 x 16384, 64 queries 38.9, 30.9, 32 26.7, 30.7.
 // The int8 kernel never beat the fp4 one: AUTO takes it only where the fp4 tile
 // cannot hold the rows, from half a tile of 64 queries.
 int resolve_backend(const fid_ctx* ctx, const fid_db* db, int64_t n, int32_t n_q, Reduce what)
@@ -320,9 +323,12 @@ int resolve_backend(const fid_ctx* ctx, const fid_db* db, int64_t n, int32_t n_q
         return int8 ? FID_BACKEND_MFMA : FID_BACKEND_POPCOUNT;
     }
     int32_t least = what == kCounts ? std::clamp(12288 / L, 2, 32) : std::clamp(24576 / L, 4, 48);
-    if (n <= 8192) least = 512;
-    else if (n <= (L > 2048 ? 0 : L > 1024 ? 12288 : L > 512 ? 32768 : 49152)) least = 256;
-    else if (n <= 32768) least = std::max(least, 8);
+    int64_t work = 0;   // least counts x loci
+    if (n <= 65536) {
+        work = L > 1024 && n > 16384 ? 1ll << 29 : 1ll << 30;
+        if (n <= 8192) work = work / 4096 * std::max(L, 4096);
+    }
+    if (n * n_q * L < work) return FID_BACKEND_POPCOUNT;
     return n_q >= least ? FID_BACKEND_MFMA_FP4 : FID_BACKEND_POPCOUNT;
 }
 
@@ -342,9 +348,14 @@ Job make_job(const fid_ctx* ctx, const fid_db* db, int32_t n_q, Reduce what)
 
 Plan plan_fp4(int num_cus, int64_t r_lo, int64_t r_hi, int32_t nq, int epi)
 {
-    const int64_t n_qtiles = (nq + fp4_queries_per_wg() - 1) / fp4_queries_per_wg();
+    int64_t n_qtiles = (nq + fp4_queries_per_wg() - 1) / fp4_queries_per_wg();
     const int64_t base = (r_lo / kDbTileRefs) * kDbTileRefs;
     const int64_t ntiles = (r_hi - base + fp4_refs_per_wg() - 1) / fp4_refs_per_wg();
+    // A short range's 512-reference tiles leave CUs idle: more query tiles, down
+    // to one block of 16, as far as there are CUs (all counts, 20k x 2048
+    // loci, 40 reference tiles: 64 queries 13.3 -> 9.7 us, 128 20.3 -> 11.3, 256
+    // 21.3 -> 14.3).
+    n_qtiles = std::max(n_qtiles, std::min<int64_t>((nq + 15) / 16, num_cus / ntiles));
     const int64_t target = (int64_t)num_cus * env_int("FASTID_MFMA_WG_PER_CU", 2, 1, 64);
     int64_t rsplit = std::max<int64_t>(1, target / n_qtiles);
     rsplit = std::min(rsplit, ntiles);
@@ -353,6 +364,7 @@ Plan plan_fp4(int num_cus, int64_t r_lo, int64_t r_hi, int32_t nq, int epi)
     if (rsplit * n_qtiles > (int64_t)(1 << 30)) return p;
     p.n_rsplit = (int32_t)rsplit;
     p.q_per_worker = fp4_queries_per_wg();
+    p.n_qtiles = (int32_t)n_qtiles;
     p.n_workers = (int32_t)(rsplit * n_qtiles);
     p.list_workers = p.n_rsplit * fp4_list_workers_per_wg();
     return p;
@@ -380,6 +392,7 @@ ScanParams make_params(const fid_db* db, const Job& j, const Plan& pl, int64_t r
     p.q_lo = q_lo;
     p.q_hi = q_hi;
     p.n_rsplit = pl.n_rsplit;
+    p.n_qtiles = pl.n_qtiles;
     p.q_per_worker = pl.q_per_worker;
     p.n_workers = pl.n_workers;
     p.lds_words_per_wave = pl.lds_words_per_wave;

@@ -60,6 +60,7 @@ struct ScanParams {
     int64_t blk_lo, nblk;  // blocks covering [r_lo, r_hi)
     int32_t q_lo, q_hi;
     int32_t n_rsplit;      // workers along the reference axis
+    int32_t n_qtiles;            // query tiles of an fp4 scan
     int32_t q_per_worker;  // queries per worker
     int32_t n_workers;
     int32_t lds_words_per_wave;

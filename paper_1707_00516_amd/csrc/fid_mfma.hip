@@ -1200,7 +1200,7 @@ __global__ __launch_bounds__(kWGM) void fp4_scan_kernel(
     uint64_t* __restrict__ hit_keys, int32_t* __restrict__ hit_cnt)
 {
     const int n_q = p.q_hi - p.q_lo;
-    const int n_qtiles = (n_q + kQB4 - 1) / kQB4;
+    const int n_qtiles = p.n_qtiles;
     const int wg = xcd_local_index((int)blockIdx.x, (int)gridDim.x);
     const int qt_idx = wg % n_qtiles;
     const int wr_g = wg / n_qtiles;
@@ -1448,8 +1448,7 @@ int fp4_list_workers_per_wg() { return kWavesM; }
 template <int EPI, bool KCHUNKS, int NA>
 static hipError_t launch_fp4_t(int mode, const ScanParams& p, const MfmaBuffers& b, hipStream_t s)
 {
-    const int n_qtiles = (p.q_hi - p.q_lo + kQB4 - 1) / kQB4;
-    const int64_t blocks = (int64_t)n_qtiles * p.n_rsplit;
+    const int64_t blocks = (int64_t)p.n_qtiles * p.n_rsplit;
     const hipError_t e = lds_opt_in<&fp4_scan_kernel<EPI, KCHUNKS, NA>>((int)kLdsFp4);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((fp4_scan_kernel<EPI, KCHUNKS, NA>), dim3((unsigned)blocks), dim3(kWGM), kLdsFp4, s, p, mode,
@@ -1462,8 +1461,7 @@ static hipError_t launch_fp4_t(int mode, const ScanParams& p, const MfmaBuffers&
 template <int EPI, bool KCHUNKS>
 static hipError_t launch_fp4_na(int mode, const ScanParams& p, const MfmaBuffers& b, hipStream_t s)
 {
-    const int blocks = fp4_tile_blocks(p.q_hi - p.q_lo), n_qtiles = (p.q_hi - p.q_lo + kQB4 - 1) / kQB4;
-    switch ((blocks + n_qtiles - 1) / n_qtiles) {
+    switch ((fp4_tile_blocks(p.q_hi - p.q_lo) + p.n_qtiles - 1) / p.n_qtiles) {
         case 1:
         case 2: return launch_fp4_t<EPI, KCHUNKS, 2>(mode, p, b, s);
         case 3:
@@ -1490,6 +1488,9 @@ hipError_t launch_fp4_scan(int mode, int epi, const ScanParams& p, const MfmaBuf
                            hipStream_t s)
 {
     if (p.n_rsplit <= 0) return hipSuccess;
+    // (no tile of more queries than it holds, none without)
+    if (p.n_qtiles < (p.q_hi - p.q_lo + kQB4 - 1) / kQB4 || p.n_qtiles > fp4_tile_blocks(p.q_hi - p.q_lo))
+        return hipErrorInvalidValue;
     if (b.kpad > kMaxKpad4 || b.kpad != fp4_kpad(p.db.n_loci)) return hipErrorInvalidValue;
     if (b.kpad > 2 * kHalfLoci4) return launch_fp4_k<true>(mode, epi, p, b, s);
     return launch_fp4_k<false>(mode, epi, p, b, s);

@@ -25,9 +25,9 @@ def ctx():
 
 
 @pytest.mark.parametrize("n,L,n_q", [
-    (8192, 2048, 511), (8192, 2048, 512), (8193, 3000, 7), (8193, 3000, 8), (12288, 2048, 255), (12289, 2048, 8),
-    (16384, 300, 256), (16385, 300, 255), (32768, 1024, 256), (32769, 1024, 11), (32769, 1024, 12), (49152, 300, 32),
-    (49153, 300, 32), (131072, 64, 3), (131073, 64, 3), (131072, 64, 127), (262144, 64, 200), (262144, 64, 201),
+    (8192, 8192, 31), (8192, 8192, 32), (8193, 3000, 43), (8193, 3000, 44), (16384, 2048, 31), (16384, 2048, 32),
+    (16385, 2048, 15), (16385, 2048, 16), (32768, 1024, 32), (32769, 1024, 31), (65536, 300, 54), (65536, 300, 55),
+    (65537, 300, 31), (65537, 300, 32), (513, 2048, 300), (2000, 1024, 600), (40_000, 100, 300), (131072, 64, 3), (131073, 64, 3), (131072, 64, 127), (262144, 64, 200), (262144, 64, 201),
     (262145, 64, 200), (262144, 2048, 5), (262144, 2048, 6), (262145, 2048, 11), (262145, 2048, 12), (33000, 5000, 2),
     (33000, 5000, 1), (540_000, 300, 64), (400_001, 1000, 150), (1_200_000, 100, 17)])
 def test_routes_agree(ctx, n, L, n_q, k=5):
