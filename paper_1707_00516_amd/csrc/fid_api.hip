@@ -323,12 +323,11 @@ int resolve_backend(const fid_ctx* ctx, const fid_db* db, int64_t n, int32_t n_q
         return int8 ? FID_BACKEND_MFMA : FID_BACKEND_POPCOUNT;
     }
     int32_t least = what == kCounts ? std::clamp(12288 / L, 2, 32) : std::clamp(24576 / L, 4, 48);
-    int64_t work = 0;   // least counts x loci
     if (n <= 65536) {
-        work = L > 1024 && n > 16384 ? 1ll << 29 : 1ll << 30;
+        int64_t work = L > 1024 && n > 16384 ? 1ll << 29 : 1ll << 30;  // least counts x loci
         if (n <= 8192) work = work / 4096 * std::max(L, 4096);
+        if (n * n_q * L < work) return FID_BACKEND_POPCOUNT;
     }
-    if (n * n_q * L < work) return FID_BACKEND_POPCOUNT;
     return n_q >= least ? FID_BACKEND_MFMA_FP4 : FID_BACKEND_POPCOUNT;
 }
 
