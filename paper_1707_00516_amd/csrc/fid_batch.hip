@@ -417,6 +417,17 @@ int plan_batch(const fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
     int64_t g = 0, words = 0;
     struct Seg { BItem it; int64_t cost; bool seed; };
     std::vector<Seg> segs;
+    // Reference tiles x query tiles x loci of all jobs: an fp4 item is at most a
+    // quarter of a CU's share, or a small batch would run on a few of them (10
+    // jobs over up to 90k references: 6.9 ms with items of the table's length,
+    // 0.66 so; 33 jobs, 70k: 8.6 and 1.9; 47 jobs, 430k: 11.9 and 9.0).  Large
+    // batches keep the table's item length.
+    double f4_work = 0;
+    for (int32_t j = 0; j < n_jobs; ++j)
+        if (jobs[j].db && jobs[j].r_hi > jobs[j].r_lo && jobs[j].n_q > 0)
+            f4_work += ((double)(jobs[j].r_hi - jobs[j].r_lo) / fp4_refs_per_wg() + 1) *
+                       ((jobs[j].n_q + fp4_queries_per_wg() - 1) / fp4_queries_per_wg()) *
+                       fp4_kpad(jobs[j].db->v.n_loci);
     for (int32_t j = 0; j < n_jobs; ++j) {
         const fid_job& J = jobs[j];
         if (!J.db) return fail(FID_EINVAL, "job %d: db is NULL", j);
@@ -444,6 +455,8 @@ int plan_batch(const fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
             f.kpad = fp4_kpad(f.n_loci);
             const fid_tune* t = find_tune(tune, n_tune, f.n_loci);
             f.tiles = t && t->fp4_tiles > 0 ? t->fp4_tiles : kFp4DefaultTiles;
+            f.tiles = (int32_t)std::min<double>(
+                f.tiles, std::max<double>(f.kpad > 2048 ? 2 : 4, f4_work / (4.0 * ctx->num_cus * f.kpad)));
             f.seed = seed_prefix(J.r_hi - J.r_lo, FID_BACKEND_MFMA_FP4, J.n_q);
             f.direct = f.seed == J.r_hi - J.r_lo;
             f.qtiles = (f.n_q + fp4_queries_per_wg() - 1) / fp4_queries_per_wg();

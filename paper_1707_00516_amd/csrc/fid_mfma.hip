@@ -621,8 +621,8 @@ __device__ __forceinline__ uint32_t word_of(const uint4& v, int t)
     return t == 0 ? v.x : t == 1 ? v.y : t == 2 ? v.z : v.w;
 }
 
-// Query tiles: the 16-query blocks of [0, n_q) dealt evenly to
-// ceil(n_q / 128) tiles, so that 131 queries run as tiles of 5 and 4 blocks
+// Query tiles: the 16-query blocks of [0, n_q) dealt evenly to a launch's
+// tiles (ceil(n_q / 128) of them, more over a short range), so that 131 queries run as tiles of 5 and 4 blocks
 // and not as 8 and 1 (whose references are read, spread and checked for
 // 3 queries).
 __host__ __device__ inline int fp4_tile_blocks(int n_q) { return (n_q + 15) / 16; }
@@ -771,10 +771,10 @@ static_assert(kLdsFp4 + 16 <= 163840, "fp4 query tile and epilogue state must fi
 // read before every four MFMAs), the LDS words are permuted so that no read
 // meets a bank twice, and the next half of a long row is copied by the DMA
 // engine under the current one.  Measured at 2048 x 20M x 2048, top-32 (the
-// scan alone): 23.1 ms before, 21.9 ms now, MFMA pipes busy 0.73 -> 0.80 of the
-// time; 256 x 2M x 32768 5.53 -> 5.05 ms; 2048 x 1M x 2048 full counts 3.75 ->
-// 2.68 ms (16-byte stores); 131 x 20M x 2048 3.17 -> 2.1 ms (tiles of 5 and 4
-// blocks).
+// scan alone): 23.1 ms before, 21.9 with these, MFMA pipes busy 0.73 -> 0.80 of
+// the time, 20.8 with fewer and cheaper visits to the selection; 256 x 2M x
+// 32768 5.53 -> 4.95 ms; 2048 x 1M x 2048 full counts 3.75 -> 2.68 ms (16-byte
+// stores); 131 x 20M x 2048 3.17 -> 2.0 ms (tiles of 5 and 4 blocks).
 template <int EPI, bool KCHUNKS, int NA>
 __device__ __forceinline__ void fp4_work(const Fp4Work& w)
 {
