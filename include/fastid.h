@@ -82,9 +82,8 @@ typedef enum {
  * MFMA_FP4: the same closed form with 0/1 operands in fp4 (e2m1) on the
  *   f8f6f4 matrix cores, fp32 accumulation (exact: sums stay below 2^24).
  * MFMA covers L <= 2304 (longer rows run POPCOUNT); MFMA_FP4 covers every L
- * (rows over 2048 loci stage the query tile in 2048-locus chunks).  AUTO picks per
- * call from the problem shape (row length, query-tile fill).  Results are
- * identical whatever the family.
+ * (rows over 2048 loci stage the query tile in 1024-locus halves).  AUTO picks per
+ * call from the problem's sizes.  Results are identical whatever the family.
  */
 typedef enum {
     FID_BACKEND_AUTO = 0,
@@ -121,8 +120,8 @@ int fid_ctx_destroy(fid_ctx* ctx);
 int fid_ctx_set_backend(fid_ctx* ctx, int backend);
 
 /*
- * The kernel family (fid_backend, never AUTO) a comparison of n_q queries
- * against db would use on this context now.
+ * The kernel family (fid_backend, never AUTO) a top-k of n_q queries against
+ * db would use on this context now, given the workspace it asks for.
  */
 int fid_backend_for(fid_ctx* ctx, const fid_db* db, int32_t n_q, int* backend);
 
@@ -349,9 +348,9 @@ int fid_compare_topk(fid_ctx* ctx, const fid_db* db, const uint64_t* q_dev, int3
  * the top-k workspace live in a fixed 256 MiB array that every device holds
  * from the library's load until the process ends; the call allocates nothing
  * (no hipMalloc, hipFree or allocating library routine).  The array must hold
- * fid_topk_workspace_bytes() plus the staged queries (at most n_q x L/2 bytes
- * + 4 n_q, 256-byte aligned): e.g. up to 256 queries against 20M references at
- * 2048 loci and k = 32.  Larger problems return FID_ENOMEM, with the bytes
+ * the workspace of a list scan (k-slot lists and the seed's counts) plus the
+ * staged queries (at most n_q x L/2 bytes + 4 n_q, 256-byte aligned): e.g. up to
+ * 240 queries against 20M references at 2048 loci and k = 32.  Larger problems return FID_ENOMEM, with the bytes
  * needed in fid_last_error(), before anything is enqueued.  Every call on a
  * device shares that device's array: calls that overlap on one device (two
  * streams, two contexts or two threads) race and must be ordered by the
@@ -509,7 +508,7 @@ int fid_batch_workspace_bytes(fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs,
  * kernel where it holds the rows, below; FID_BACKEND_POPCOUNT: the
  * persistent popcount launch, below).  Batched fp4 work
  * items are (job, 128-query tile, run of at most fp4_tiles 512-reference
- * tiles), the items of one reference run queued together on one XCD's
+ * tiles, fewer where the batch is small), the items of one reference run queued together on one XCD's
  * queue, the runs dealt largest first to the least-loaded queue.  Jobs sent
  * to the int8 matrix cores run as
  * per-call top-k (fid_compare_topk_range) inside the batch, spread over up to
