@@ -682,19 +682,23 @@ __device__ __forceinline__ T* uni(T* p)
 // LDS at the wave-uniform byte address lds.  Written as assembly because the
 // compiler makes every LDS read that follows the builtin wait for all loads
 // in flight; here the LDS halves alternate, and the wait (vmcnt 0, before the
-// workgroup barrier that hands a half over) is the caller's.  No register is
-// written, and a wait the compiler places for its own loads can only get
-// stricter by loads it does not know of.
+// workgroup barrier that hands a half over) is the caller's.  No vector
+// register is written, and a wait the compiler places for its own loads can
+// only get stricter by loads it does not know of.  The s_nop stands for two
+// hazards that the hardware leaves to the program, and that the compiler does
+// not look for inside assembly: one wait state from the write of m0 to a load
+// into LDS, and five from a VALU write of a scalar register (the base comes
+// from v_readfirstlane) to a vector memory instruction that reads it.
 __device__ __forceinline__ void dma16(uint32_t lds, const void* base, uint32_t off)
 {
-    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
                      :
                      : "s"(uni((int32_t)lds)), "v"(off), "s"(uni(base))
                      : "memory");
 }
 __device__ __forceinline__ void dma4(uint32_t lds, const void* base, uint32_t off)
 {
-    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2"
                      :
                      : "s"(uni((int32_t)lds)), "v"(off), "s"(uni(base))
                      : "memory");
