@@ -642,10 +642,12 @@ bool direct_pays(int backend, int64_t n, int32_t n_q)
 }
 
 // A top-k call's family and layout: what is fastest of what fits.  A workspace
-// too small for all counts holds the lists, with a seed as long as it has
-// room for, and one that was sized for the
-// popcount scan (a call with another number of queries) still serves it, so
-// that a workspace kept for several calls is not refused.
+// too small for all counts holds the lists, with a seed as long as it has room
+// for, and one too small for the lists of the faster family those of the other:
+// where the families cross, either may need less (20M x 2048 loci, top-32: 11
+// queries take 29.1 MB of popcount lists, or 17.5 MB of fp4 ones, of which 12
+// take 19.1), so a workspace sized for more queries is not refused because
+// fewer would run faster elsewhere.
 struct TopkPick {
     Job j;
     TopkLayout L;
@@ -686,8 +688,10 @@ TopkPick pick_topk(const fid_ctx* ctx, const fid_db* db, int64_t r_lo, int64_t r
     if (b == FID_BACKEND_MFMA_FP4 && fits(b, long_seed_refs(n, n_q, db->v.n_loci))) return p;
     if (fits(b, seed_refs(n, b, n_q))) return p;
     first = p;
-    if (b == FID_BACKEND_MFMA_FP4 && forced_backend(ctx, db) == FID_BACKEND_AUTO &&
-        fits(FID_BACKEND_POPCOUNT, seed_refs(n, FID_BACKEND_POPCOUNT, n_q)))
+    const int other = b == FID_BACKEND_MFMA_FP4 ? FID_BACKEND_POPCOUNT : FID_BACKEND_MFMA_FP4;
+    if (forced_backend(ctx, db) == FID_BACKEND_AUTO &&
+        (other == FID_BACKEND_POPCOUNT || fp4_kpad(db->v.n_loci) <= fp4_max_kpad()) &&
+        fits(other, seed_refs(n, other, n_q)))
         return p;
     // a workspace sized by a call without a bound
     if (scan && !with_queries && direct_pays(b, n, n_q) && fits(b, n)) return p;
