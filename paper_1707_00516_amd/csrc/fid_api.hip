@@ -1477,9 +1477,11 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
     const int64_t blk = std::min(block_refs, n_refs);
     const int64_t n_blocks = (n_refs + blk - 1) / blk;
 
-    FID_TRY(ensure_copy_streams(ctx, 4, 9));
-    const hipStream_t* const h2d = ctx->copy_stream;
-    const hipStream_t* const d2h = ctx->copy_stream + 2;
+    // one stream each way: the counts going out take nearly all of the time, and
+    // on two streams in turn their copies get in each other's way (512 queries x
+    // 400k references in seven blocks: 16.0-16.3 ms, 15.2 on one)
+    FID_TRY(ensure_copy_streams(ctx, 2, 9));
+    const hipStream_t h2d = ctx->copy_stream[0], d2h = ctx->copy_stream[1];
     const hipEvent_t* const ev = ctx->copy_event;
     const hipEvent_t copied[2] = {ev[0], ev[1]}, built[2] = {ev[2], ev[3]}, counted[2] = {ev[4], ev[5]},
                      shipped[2] = {ev[6], ev[7]}, start = ev[8];
@@ -1489,7 +1491,7 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
     };
     // the copy streams start after everything already queued on the context
     hip(hipEventRecord(start, ctx->stream), "hipEventRecord");
-    for (int i = 0; i < 4 && !st; ++i) hip(hipStreamWaitEvent(ctx->copy_stream[i], start, 0), "hipStreamWaitEvent");
+    for (int i = 0; i < 2 && !st; ++i) hip(hipStreamWaitEvent(ctx->copy_stream[i], start, 0), "hipStreamWaitEvent");
     for (int64_t b = 0; b < n_blocks && !st; ++b) {
         const int slot = (int)(b & 1);
         const int64_t r0 = b * blk;
@@ -1497,11 +1499,11 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
         uint64_t* stage = reinterpret_cast<uint64_t*>(ws + L.off_stage[slot]);
         int32_t* out = reinterpret_cast<int32_t*>(ws + L.off_out[slot]);
         // rows in: the slot is free once block b - 2 has been built from it
-        if (b >= 2) hip(hipStreamWaitEvent(h2d[slot], built[slot], 0), "hipStreamWaitEvent");
+        if (b >= 2) hip(hipStreamWaitEvent(h2d, built[slot], 0), "hipStreamWaitEvent");
         if (!st)
             hip(hipMemcpyAsync(stage, rows_host + r0 * rw, (size_t)n * (size_t)rw * sizeof(uint64_t),
-                               hipMemcpyHostToDevice, h2d[slot]), "block copy");
-        if (!st) hip(hipEventRecord(copied[slot], h2d[slot]), "hipEventRecord");
+                               hipMemcpyHostToDevice, h2d), "block copy");
+        if (!st) hip(hipEventRecord(copied[slot], h2d), "hipEventRecord");
         // build and count: the count slot is free once block b - 2's counts shipped
         if (!st) hip(hipStreamWaitEvent(ctx->stream, copied[slot], 0), "hipStreamWaitEvent");
         if (!st && b >= 2) hip(hipStreamWaitEvent(ctx->stream, shipped[slot], 0), "hipStreamWaitEvent");
@@ -1514,15 +1516,15 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
         delete db;  // the host handle only: the launches took its view by value
         if (!st) hip(hipEventRecord(counted[slot], ctx->stream), "hipEventRecord");
         // counts out: [n_q][n] into columns [r0, r0 + n) of the caller's rows
-        if (!st) hip(hipStreamWaitEvent(d2h[slot], counted[slot], 0), "hipStreamWaitEvent");
+        if (!st) hip(hipStreamWaitEvent(d2h, counted[slot], 0), "hipStreamWaitEvent");
         if (!st)
             hip(hipMemcpy2DAsync(counts_host + r0, (size_t)ld * sizeof(int32_t), out, (size_t)n * sizeof(int32_t),
-                                 (size_t)n * sizeof(int32_t), (size_t)n_q, hipMemcpyDeviceToHost, d2h[slot]),
+                                 (size_t)n * sizeof(int32_t), (size_t)n_q, hipMemcpyDeviceToHost, d2h),
                 "counts copy");
-        if (!st) hip(hipEventRecord(shipped[slot], d2h[slot]), "hipEventRecord");
+        if (!st) hip(hipEventRecord(shipped[slot], d2h), "hipEventRecord");
     }
     // every copy has run before the host buffers are handed back
-    for (int i = 0; i < 4; ++i) hip(hipStreamSynchronize(ctx->copy_stream[i]), "hipStreamSynchronize");
+    for (int i = 0; i < 2; ++i) hip(hipStreamSynchronize(ctx->copy_stream[i]), "hipStreamSynchronize");
     hip(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
     return st;
 }
