@@ -129,6 +129,102 @@ void give_host_word(unsigned long long* w)
     else (void)hipHostFree(w);
 }
 
+// Copy streams of the streamed calls.  A new stream can cost its caller a new
+// hardware queue (3 ms, and as much again at its first copy), so a call borrows
+// streams from its device's pool, which hold no work in between, and gives them
+// back at its end.  A call beside others makes what it lacks; kCopyStreamsKept
+// stay in the pool until the device's last context is destroyed.
+constexpr int kCopyStreamsKept = 4;
+constexpr int kPoolDevices = 64;  // a device beyond these keeps none
+struct CopyPool {
+    int contexts, n;
+    int64_t calls;  // that wanted a second stream
+    hipStream_t idle[kCopyStreamsKept];
+};
+std::mutex g_copy_mu;
+CopyPool g_copy_pools[kPoolDevices];
+
+CopyPool* copy_pool(int device) { return device < kPoolDevices ? &g_copy_pools[device] : nullptr; }
+
+void copy_pool_enter(int device)
+{
+    std::lock_guard<std::mutex> lk(g_copy_mu);
+    if (CopyPool* p = copy_pool(device)) ++p->contexts;
+}
+
+void copy_pool_leave(int device)
+{
+    std::lock_guard<std::mutex> lk(g_copy_mu);
+    CopyPool* p = copy_pool(device);
+    if (!p || --p->contexts > 0) return;
+    while (p->n > 0) (void)hipStreamDestroy(p->idle[--p->n]);
+}
+
+class CopyStreams {
+public:
+    explicit CopyStreams(const fid_ctx* ctx) : pool_(copy_pool(ctx->device)) {}
+    CopyStreams(const CopyStreams&) = delete;
+    CopyStreams& operator=(const CopyStreams&) = delete;
+    ~CopyStreams()
+    {
+        while (n_ > 0) give(s_[--n_]);
+    }
+    // At least `least` streams, up to `most` of them if the pool holds them.
+    int take(int least, int most)
+    {
+        {
+            std::lock_guard<std::mutex> lk(g_copy_mu);
+            while (pool_ && n_ < most && pool_->n > 0) s_[n_++] = pool_->idle[--pool_->n];
+        }
+        for (; n_ < least; ++n_)
+            FID_HIP(hipStreamCreateWithFlags(&s_[n_], hipStreamNonBlocking), "hipStreamCreate");
+        return FID_OK;
+    }
+    // To be called while this call's copies run: a second stream for the calls
+    // to come if this one would have used it and is not the first of its kind
+    // (without it they do as this one did).
+    void grow_pool(bool wanted)
+    {
+        if (!pool_ || !wanted || n_ > 1) return;
+        {
+            std::lock_guard<std::mutex> lk(g_copy_mu);
+            if (pool_->calls++ == 0) return;
+        }
+        hipStream_t s;
+        if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess) give(s);
+        else (void)hipGetLastError();
+    }
+    int count() const { return n_; }
+    // The stream of staging slot `slot`.
+    hipStream_t of(int slot) const { return s_[slot % n_]; }
+
+private:
+    void give(hipStream_t s)
+    {
+        {
+            std::lock_guard<std::mutex> lk(g_copy_mu);
+            if (pool_ && pool_->n < kCopyStreamsKept) {
+                pool_->idle[pool_->n++] = s;
+                return;
+            }
+        }
+        (void)hipStreamDestroy(s);
+    }
+    CopyPool* pool_;
+    int n_ = 0;
+    hipStream_t s_[2];
+};
+
+// A database streamed in at least three blocks is copied on two streams in
+// turn, where the pool holds two: a stream starts a copy up to 0.45 ms after its
+// last one has ended, which the other stream's copy fills (1M x 2048 loci in
+// eight blocks: 8.3 ms on one stream, 6.3 on two where PCIe moves them in 4.5; on
+// another host 4.9 and 4.7, with copies of 4.6).  Made before a process's first
+// copies the second stream would cost that call 8 ms, so a program's only call
+// does without it; its second call makes it while its copies run, and the third
+// pays 4 ms for the stream's first copies.
+constexpr int64_t kTwoStreamBlocks = 3;
+
 }  // namespace
 
 namespace {
@@ -735,15 +831,9 @@ int finish_hits(fid_ctx* ctx, const unsigned long long* counter, uint64_t* keys,
     return FID_OK;
 }
 
-// The context's first n copy streams and m events.  Successive blocks are
-// copied on two streams in turn: a stream starts a copy up to 0.45 ms after
-// its last one has ended, which the other stream's copy fills (1M x 2048 loci
-// in eight blocks: 8.3 ms per call on one stream, PCIe moves them in 4.5).
-int ensure_copy_streams(fid_ctx* ctx, int n, int m)
+// The context's first m events of the streamed calls.
+int ensure_copy_events(fid_ctx* ctx, int m)
 {
-    for (int i = 0; i < n; ++i)
-        if (!ctx->copy_stream[i])
-            FID_HIP(hipStreamCreateWithFlags(&ctx->copy_stream[i], hipStreamNonBlocking), "hipStreamCreate");
     for (int i = 0; i < m; ++i)
         if (!ctx->copy_event[i])
             FID_HIP(hipEventCreateWithFlags(&ctx->copy_event[i], hipEventDisableTiming), "hipEventCreate");
@@ -986,6 +1076,7 @@ int fid_ctx_create(fid_ctx** out, int device, void* stream)
         delete c;
         return st;
     }
+    copy_pool_enter(device);
     *out = c;
     return FID_OK;
 }
@@ -998,8 +1089,6 @@ int fid_ctx_destroy(fid_ctx* ctx)
         hipStreamSynchronize(ctx->stream);
         if (ctx->scratch) hipFree(ctx->scratch);
         give_host_word(ctx->host_word);
-        for (hipStream_t cs : ctx->copy_stream)
-            if (cs) hipStreamDestroy(cs);
         for (hipEvent_t ev : ctx->copy_event)
             if (ev) hipEventDestroy(ev);
         for (auto& ev : ctx->events) {
@@ -1007,6 +1096,7 @@ int fid_ctx_destroy(fid_ctx* ctx)
             hipEventDestroy(ev.second);
         }
     }
+    copy_pool_leave(ctx->device);
     delete ctx;
     return st;
 }
@@ -1370,8 +1460,9 @@ int fid_compare_topk_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
     int32_t* tcnt = reinterpret_cast<int32_t*>(ws + L.off_tcnt);
     int64_t* tidx = reinterpret_cast<int64_t*>(ws + L.off_tidx);
 
-    FID_TRY(ensure_copy_streams(ctx, 2, 4));
-    const hipStream_t* const copy = ctx->copy_stream;
+    FID_TRY(ensure_copy_events(ctx, 4));
+    CopyStreams copy(ctx);
+    FID_TRY(copy.take(1, n_blocks >= kTwoStreamBlocks ? 2 : 1));
     const hipEvent_t copied[2] = {ctx->copy_event[0], ctx->copy_event[1]};
     const hipEvent_t freed[2] = {ctx->copy_event[2], ctx->copy_event[3]};
     int st = FID_OK;
@@ -1381,18 +1472,18 @@ int fid_compare_topk_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
     if (!st) hip(launch_reset_running(nullptr, n_q, k, running, bound, ctx->stream), "reset launch");
     // the copy streams start after everything already queued on the context
     if (!st) hip(hipEventRecord(freed[1], ctx->stream), "hipEventRecord");
-    for (int i = 0; i < 2 && !st; ++i) hip(hipStreamWaitEvent(copy[i], freed[1], 0), "hipStreamWaitEvent");
+    for (int i = 0; i < copy.count() && !st; ++i) hip(hipStreamWaitEvent(copy.of(i), freed[1], 0), "hipStreamWaitEvent");
     for (int64_t b = 0; b < n_blocks && !st; ++b) {
         const int slot = (int)(b & 1);
         const int64_t r0 = b * blk;
         const int64_t n = std::min(blk, n_refs - r0);
         uint64_t* stage = reinterpret_cast<uint64_t*>(ws + L.off_stage[slot]);
         // block b's copy waits until block b - 2 has been built from this slot
-        if (b >= 2) hip(hipStreamWaitEvent(copy[slot], freed[slot], 0), "hipStreamWaitEvent");
+        if (b >= 2) hip(hipStreamWaitEvent(copy.of(slot), freed[slot], 0), "hipStreamWaitEvent");
         if (!st)
             hip(hipMemcpyAsync(stage, rows_host + r0 * rw, (size_t)n * (size_t)rw * sizeof(uint64_t),
-                               hipMemcpyHostToDevice, copy[slot]), "block copy");
-        if (!st) hip(hipEventRecord(copied[slot], copy[slot]), "hipEventRecord");
+                               hipMemcpyHostToDevice, copy.of(slot)), "block copy");
+        if (!st) hip(hipEventRecord(copied[slot], copy.of(slot)), "hipEventRecord");
         if (!st) hip(hipStreamWaitEvent(ctx->stream, copied[slot], 0), "hipStreamWaitEvent");
         if (st) break;
         fid_db* db = nullptr;
@@ -1408,7 +1499,8 @@ int fid_compare_topk_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
     }
     if (!st) hip(launch_finalize_topk(running, nullptr, n_q, k, k, cnt_dev, idx_dev, ctx->stream), "finalize launch");
     // the host rows must stay untouched until every copy has run
-    for (int i = 0; i < 2; ++i) hip(hipStreamSynchronize(copy[i]), "hipStreamSynchronize");
+    copy.grow_pool(n_blocks >= kTwoStreamBlocks);
+    for (int i = 0; i < copy.count(); ++i) hip(hipStreamSynchronize(copy.of(i)), "hipStreamSynchronize");
     hip(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
     return st;
 }
@@ -1480,8 +1572,10 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
     // one stream each way: the counts going out take nearly all of the time, and
     // on two streams in turn their copies get in each other's way (512 queries x
     // 400k references in seven blocks: 16.0-16.3 ms, 15.2 on one)
-    FID_TRY(ensure_copy_streams(ctx, 2, 9));
-    const hipStream_t h2d = ctx->copy_stream[0], d2h = ctx->copy_stream[1];
+    FID_TRY(ensure_copy_events(ctx, 9));
+    CopyStreams copy(ctx);
+    FID_TRY(copy.take(2, 2));
+    const hipStream_t h2d = copy.of(0), d2h = copy.of(1);
     const hipEvent_t* const ev = ctx->copy_event;
     const hipEvent_t copied[2] = {ev[0], ev[1]}, built[2] = {ev[2], ev[3]}, counted[2] = {ev[4], ev[5]},
                      shipped[2] = {ev[6], ev[7]}, start = ev[8];
@@ -1491,7 +1585,7 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
     };
     // the copy streams start after everything already queued on the context
     hip(hipEventRecord(start, ctx->stream), "hipEventRecord");
-    for (int i = 0; i < 2 && !st; ++i) hip(hipStreamWaitEvent(ctx->copy_stream[i], start, 0), "hipStreamWaitEvent");
+    for (int i = 0; i < 2 && !st; ++i) hip(hipStreamWaitEvent(copy.of(i), start, 0), "hipStreamWaitEvent");
     for (int64_t b = 0; b < n_blocks && !st; ++b) {
         const int slot = (int)(b & 1);
         const int64_t r0 = b * blk;
@@ -1524,7 +1618,7 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
         if (!st) hip(hipEventRecord(shipped[slot], d2h), "hipEventRecord");
     }
     // every copy has run before the host buffers are handed back
-    for (int i = 0; i < 2; ++i) hip(hipStreamSynchronize(ctx->copy_stream[i]), "hipStreamSynchronize");
+    for (int i = 0; i < 2; ++i) hip(hipStreamSynchronize(copy.of(i)), "hipStreamSynchronize");
     hip(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
     return st;
 }
@@ -1798,8 +1892,9 @@ int fid_compare_threshold_streamed(fid_ctx* ctx, const uint64_t* rows_host, int6
     int32_t* vals2 = reinterpret_cast<int32_t*>(take(c * sizeof(int32_t)));
     int64_t* ends = reinterpret_cast<int64_t*>(take((size_t)(n_blocks + 1) * sizeof(int64_t)));
 
-    FID_TRY(ensure_copy_streams(ctx, 2, 4));
-    const hipStream_t* const copy = ctx->copy_stream;
+    FID_TRY(ensure_copy_events(ctx, 4));
+    CopyStreams copy(ctx);
+    FID_TRY(copy.take(1, n_blocks >= kTwoStreamBlocks ? 2 : 1));
     const hipEvent_t copied[2] = {ctx->copy_event[0], ctx->copy_event[1]};
     const hipEvent_t freed[2] = {ctx->copy_event[2], ctx->copy_event[3]};
     int st = FID_OK;
@@ -1809,18 +1904,18 @@ int fid_compare_threshold_streamed(fid_ctx* ctx, const uint64_t* rows_host, int6
     if (!st) hip(launch_fill_u64(reinterpret_cast<uint64_t*>(counter), 1, 0ull, ctx->stream), "fill launch");
     if (!st) hip(launch_fill_u64(reinterpret_cast<uint64_t*>(ends), 1, 0ull, ctx->stream), "fill launch");
     if (!st) hip(hipEventRecord(freed[1], ctx->stream), "hipEventRecord");
-    for (int i = 0; i < 2 && !st; ++i) hip(hipStreamWaitEvent(copy[i], freed[1], 0), "hipStreamWaitEvent");
+    for (int i = 0; i < copy.count() && !st; ++i) hip(hipStreamWaitEvent(copy.of(i), freed[1], 0), "hipStreamWaitEvent");
     Prepared q;
     Job j{};
     for (int64_t b = 0; b < n_blocks && !st; ++b) {
         const int slot = (int)(b & 1);
         const int64_t r0 = b * blk;
         const int64_t n = std::min(blk, n_refs - r0);
-        if (b >= 2) hip(hipStreamWaitEvent(copy[slot], freed[slot], 0), "hipStreamWaitEvent");
+        if (b >= 2) hip(hipStreamWaitEvent(copy.of(slot), freed[slot], 0), "hipStreamWaitEvent");
         if (!st)
             hip(hipMemcpyAsync(stage[slot], rows_host + r0 * rw, (size_t)n * (size_t)rw * sizeof(uint64_t),
-                               hipMemcpyHostToDevice, copy[slot]), "block copy");
-        if (!st) hip(hipEventRecord(copied[slot], copy[slot]), "hipEventRecord");
+                               hipMemcpyHostToDevice, copy.of(slot)), "block copy");
+        if (!st) hip(hipEventRecord(copied[slot], copy.of(slot)), "hipEventRecord");
         if (!st) hip(hipStreamWaitEvent(ctx->stream, copied[slot], 0), "hipStreamWaitEvent");
         if (st) break;
         fid_db* db = nullptr;
@@ -1847,7 +1942,8 @@ int fid_compare_threshold_streamed(fid_ctx* ctx, const uint64_t* rows_host, int6
         if (!st)
             hip(launch_offset_block_hits(counter, ends, (int32_t)b, keys, cap, r0, ctx->stream), "offset launch");
     }
-    for (int i = 0; i < 2; ++i) hip(hipStreamSynchronize(copy[i]), "hipStreamSynchronize");
+    copy.grow_pool(n_blocks >= kTwoStreamBlocks);
+    for (int i = 0; i < copy.count(); ++i) hip(hipStreamSynchronize(copy.of(i)), "hipStreamSynchronize");
     if (!st)
         st = finish_hits(ctx, counter, keys, vals, keys2, vals2, cap, n_q, offs_dev, idx_dev, cnt_dev, total_host);
     else

@@ -19,9 +19,8 @@ struct fid_ctx {
     std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
     size_t events_used;
     unsigned long long* host_word;  // pinned: what a kernel tells a call that waits for it
-    // copy streams and their events, made by the first streamed call and kept
-    // (a call owns them while it runs, as it owns the scratch)
-    hipStream_t copy_stream[2];
+    // events of the streamed calls, made by the first one and kept (a call owns
+    // them while it runs, as it owns the scratch)
     hipEvent_t copy_event[9];
     void* fixed_scratch;  // this device's address of the library's fixed scratch array
 };
