@@ -495,7 +495,13 @@ typedef struct {
 
 typedef struct fid_batch fid_batch;
 
-/* Device workspace bytes fid_batch_create needs for these jobs (k <= 128). */
+/*
+ * Device workspace bytes with which fid_batch_create spreads these jobs over the
+ * chip (k <= 128).  A small batch's shorter work items take up to 256 MiB of
+ * top-k lists; fid_batch_create also accepts a workspace that holds only the
+ * lists of the tuning table's item lengths (one job of 512 queries x 2M
+ * references at k = 32: 256 MiB of lists, or 31).
+ */
 int fid_batch_workspace_bytes(fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t k,
                               const fid_tune* tune, int32_t n_tune, size_t* bytes);
 
@@ -508,7 +514,8 @@ int fid_batch_workspace_bytes(fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs,
  * kernel where it holds the rows, below; FID_BACKEND_POPCOUNT: the
  * persistent popcount launch, below).  Batched fp4 work
  * items are (job, 128-query tile, run of at most fp4_tiles 512-reference
- * tiles, fewer where the batch is small), the items of one reference run queued together on one XCD's
+ * tiles, fewer where the batch is small and the workspace holds their lists),
+ * the items of one reference run queued together on one XCD's
  * queue, the runs dealt largest first to the least-loaded queue.  Jobs sent
  * to the int8 matrix cores run as
  * per-call top-k (fid_compare_topk_range) inside the batch, spread over up to

@@ -399,8 +399,15 @@ const fid_tune* find_tune(const fid_tune* tune, int32_t n_tune, int32_t n_loci)
     return any;
 }
 
+// Every (item, query, wave) of the fp4 top-k pass has a k-slot list, so shorter
+// items mean more of them: items are shortened only as far as the lists stay
+// within this, which a quarter of a CU's share reaches at k = 32 (1024 items of
+// 128 queries); at k = 128 it would take four times as much.
+constexpr double kShortItemLists = 256.0 * (1 << 20);
+
+// short_items: fp4 items shorter than the tuning table's in a small batch.
 int plan_batch(const fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t k,
-               const fid_tune* tune, int32_t n_tune, BatchPlan* P)
+               const fid_tune* tune, int32_t n_tune, BatchPlan* P, bool short_items)
 {
     if (!ctx) return fail(FID_EINVAL, "ctx is NULL");
     if (!jobs || n_jobs < 1) return fail(FID_EINVAL, "no jobs");
@@ -422,12 +429,21 @@ int plan_batch(const fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
     // jobs over up to 90k references: 6.9 ms with items of the table's length,
     // 0.66 so; 33 jobs, 70k: 8.6 and 1.9; 47 jobs, 430k: 11.9 and 9.0).  Large
     // batches keep the table's item length.
-    double f4_work = 0;
-    for (int32_t j = 0; j < n_jobs; ++j)
-        if (jobs[j].db && jobs[j].r_hi > jobs[j].r_lo && jobs[j].n_q > 0)
-            f4_work += ((double)(jobs[j].r_hi - jobs[j].r_lo) / fp4_refs_per_wg() + 1) *
-                       ((jobs[j].n_q + fp4_queries_per_wg() - 1) / fp4_queries_per_wg()) *
-                       fp4_kpad(jobs[j].db->v.n_loci);
+    double f4_work = 0, f4_lists = 0;
+    auto f4_share = [&](int kpad) {
+        return std::max<double>(kpad > 2048 ? 2 : 4, f4_work / (4.0 * ctx->num_cus * kpad));
+    };
+    for (int pass = 0; pass < 2; ++pass)
+        for (int32_t j = 0; j < n_jobs; ++j) {
+            if (!jobs[j].db || jobs[j].r_hi <= jobs[j].r_lo || jobs[j].n_q <= 0) continue;
+            const double ntiles = (double)(jobs[j].r_hi - jobs[j].r_lo) / fp4_refs_per_wg();
+            const int kpad = fp4_kpad(jobs[j].db->v.n_loci);
+            if (pass == 0)
+                f4_work += (ntiles + 1) * ((jobs[j].n_q + fp4_queries_per_wg() - 1) / fp4_queries_per_wg()) * kpad;
+            else
+                f4_lists += ntiles / f4_share(kpad) * jobs[j].n_q * fp4_list_workers_per_wg() * k * sizeof(uint64_t);
+        }
+    const double f4_stretch = std::max(1.0, f4_lists / kShortItemLists);
     for (int32_t j = 0; j < n_jobs; ++j) {
         const fid_job& J = jobs[j];
         if (!J.db) return fail(FID_EINVAL, "job %d: db is NULL", j);
@@ -455,8 +471,7 @@ int plan_batch(const fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
             f.kpad = fp4_kpad(f.n_loci);
             const fid_tune* t = find_tune(tune, n_tune, f.n_loci);
             f.tiles = t && t->fp4_tiles > 0 ? t->fp4_tiles : kFp4DefaultTiles;
-            f.tiles = (int32_t)std::min<double>(
-                f.tiles, std::max<double>(f.kpad > 2048 ? 2 : 4, f4_work / (4.0 * ctx->num_cus * f.kpad)));
+            if (short_items) f.tiles = (int32_t)std::min<double>(f.tiles, f4_share(f.kpad) * f4_stretch);
             f.seed = seed_prefix(J.r_hi - J.r_lo, FID_BACKEND_MFMA_FP4, J.n_q);
             f.direct = f.seed == J.r_hi - J.r_lo;
             f.qtiles = (f.n_q + fp4_queries_per_wg() - 1) / fp4_queries_per_wg();
@@ -717,7 +732,7 @@ int fid_batch_workspace_bytes(fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs,
 {
     if (!bytes) return fail(FID_EINVAL, "bytes is NULL");
     BatchPlan P;
-    FID_TRY(plan_batch(ctx, jobs, n_jobs, k, tune, n_tune, &P));
+    FID_TRY(plan_batch(ctx, jobs, n_jobs, k, tune, n_tune, &P, true));
     *bytes = P.total;
     return FID_OK;
 }
@@ -729,9 +744,14 @@ int fid_batch_create(fid_ctx* ctx, const fid_job* jobs, int32_t n_jobs, int32_t 
     if (!out) return fail(FID_EINVAL, "out is NULL");
     *out = nullptr;
     BatchPlan P;
-    FID_TRY(plan_batch(ctx, jobs, n_jobs, k, tune, n_tune, &P));
+    FID_TRY(plan_batch(ctx, jobs, n_jobs, k, tune, n_tune, &P, true));
     if (!ws_dev || !aligned16(ws_dev)) return fail(FID_EINVAL, "workspace NULL or not 16-byte aligned");
-    if (ws_bytes < P.total) return fail(FID_ENOMEM, "workspace %zu bytes < required %zu", ws_bytes, P.total);
+    if (ws_bytes < P.total) {  // the table's item lengths have fewer lists
+        const size_t need = P.total;
+        P = BatchPlan{};
+        FID_TRY(plan_batch(ctx, jobs, n_jobs, k, tune, n_tune, &P, false));
+        if (ws_bytes < P.total) return fail(FID_ENOMEM, "workspace %zu bytes < required %zu", ws_bytes, need);
+    }
     if ((int64_t)P.qmeta.size() > INT32_MAX) return fail(FID_EINVAL, "too many queries");
     FID_TRY(set_device(ctx));
     char* ws = static_cast<char*>(ws_dev);
