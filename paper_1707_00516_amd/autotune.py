@@ -63,6 +63,19 @@ def _time_batch(ctx, jobs, k, tune, reps, backend):
     return ev0.elapsed_time(ev1) / reps
 
 
+def _plan_bytes(ctx, jobs, k, tune, backend):
+    """Workspace of a batch's plan.  Its lists and tables grow with the number of work items: two fp4 item lengths
+    with the same workspace are the same plan."""
+    from . import FidJob, fid_batch_workspace_bytes, fid_ctx_set_backend
+    fid_ctx_set_backend(ctx.handle, backend)
+    try:
+        spec = [FidJob(j[0].handle, j[1], j[2], j[3].data_ptr(), j[3].shape[0], j[4], j[3].data_ptr(),
+                       j[3].data_ptr()) for j in jobs]
+        return fid_batch_workspace_bytes(ctx.handle, spec, k, tune)
+    finally:
+        fid_ctx_set_backend(ctx.handle, 0)
+
+
 def tune(ctx, panels: dict, queries_for, k: int = 32, n_jobs: int = 12, reps: int = 2,
          seed: int = 17, q_candidates=Q_CANDIDATES, block_candidates=BLOCK_CANDIDATES,
          fp4_tile_candidates=FP4_TILE_CANDIDATES, max_refs: int = 2_000_000, log=print):
@@ -70,8 +83,12 @@ def tune(ctx, panels: dict, queries_for, k: int = 32, n_jobs: int = 12, reps: in
     r_lo, r_hi, n_q, mode, row0)`` returns packed device query rows drawn from
     that slice.  The popcount item shape (queries x blocks) is tuned first,
     then, with it, the fp4 item length (512-reference tiles per item).
-    Returns (table, report): rows (n_loci, q_per_item, blocks_per_item,
-    fp4_tiles)."""
+    A small batch's fp4 items are no longer than a quarter of a CU's share
+    whatever the table says, so the sample decides only between lengths that
+    give it different plans, and where the longest of these wins the entry is
+    0, the library's own length (refine_fp4_on_batch finds the best one for a
+    large batch).  Returns (table, report): rows (n_loci, q_per_item,
+    blocks_per_item, fp4_tiles)."""
     import gen
     table, report = [], {}
     for L, db in sorted(panels.items()):
@@ -95,9 +112,12 @@ def tune(ctx, panels: dict, queries_for, k: int = 32, n_jobs: int = 12, reps: in
                     f"({comps * 1e3 / ms:.3e} comps/s)")
                 if best is None or ms < best[0]:
                     best = (ms, qpi, bpi)
-        best_t = None
-        for t in fp4_tile_candidates:
-            ms = _time_batch(ctx, jobs, k, [(L, best[1], best[2], t)], reps, backend=3)
+        best_t, plans = None, {}
+        for t in sorted(set(fp4_tile_candidates)):
+            plans.setdefault(_plan_bytes(ctx, jobs, k, [(L, best[1], best[2], t)], 3), []).append(t)
+        for same in plans.values():
+            t = same[0] if len(same) == 1 else 0
+            ms = _time_batch(ctx, jobs, k, [(L, best[1], best[2], same[0])], reps, backend=3)
             report[f"{L}/{best[1]}/{best[2]}/fp4:{t}"] = ms
             log(f"tune L={L} fp4_tiles={t}: {ms:.3f} ms ({comps * 1e3 / ms:.3e} comps/s)")
             if best_t is None or ms < best_t[0]:
