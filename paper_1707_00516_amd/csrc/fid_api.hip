@@ -216,13 +216,13 @@ private:
 };
 
 // A database streamed in at least three blocks is copied on two streams in
-// turn, where the pool holds two: a stream starts a copy up to 0.45 ms after its
-// last one has ended, which the other stream's copy fills (1M x 2048 loci in
-// eight blocks: 8.3 ms on one stream, 6.3 on two where PCIe moves them in 4.5; on
-// another host 4.9 and 4.7, with copies of 4.6).  Made before a process's first
-// copies the second stream would cost that call 8 ms, so a program's only call
-// does without it; its second call makes it while its copies run, and the third
-// pays 4 ms for the stream's first copies.
+// turn, where the pool holds two: a stream leaves a gap after each of its
+// copies, which the other's copy fills (1M x 2048 loci in eight blocks: 4.9 ms on
+// one stream and 4.66 on two, the copies alone 4.5; in a process that had run
+// hundreds of other calls 8.45 and 6.1).  Made before a process's first copies
+// the second stream would cost that call 8 ms, so a program's only call does
+// without it; its second call makes it while its copies run, and the third pays
+// about 4 ms for the stream's first copies.
 constexpr int64_t kTwoStreamBlocks = 3;
 
 }  // namespace
@@ -250,10 +250,16 @@ size_t db_words_bytes(int64_t nblk, int64_t row_words)
     return align256((size_t)nblk * 64 * (size_t)row_words * 8 + 4 * 64 * 16);
 }
 
-// Library scratch: staged or expanded queries.  Grown on demand.
+// Library scratch: staged or expanded queries, a page into the allocation.  A
+// context's first allocation starts at a multiple of 1 MiB, and from query rows
+// placed there the same kernel ran up to a tenth slower, presumably as their
+// scalar loads share cache sets with the database's (32 tiles of 256 x 256 of
+// 4096 loci: 43.4 us, 39.4 to 39.9 a page on).  Grown on demand.
+constexpr size_t kQueryOffset = 4096;
+
 int ensure_scratch(fid_ctx* ctx, size_t need)
 {
-    need = align256(need);
+    need = align256(need + kQueryOffset);
     if (need <= ctx->scratch_bytes) return FID_OK;
     if (ctx->scratch) {
         FID_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
@@ -271,7 +277,7 @@ int ensure_scratch(fid_ctx* ctx, size_t need)
     return FID_OK;
 }
 
-char* query_area(fid_ctx* ctx) { return static_cast<char*>(ctx->scratch); }
+char* query_area(fid_ctx* ctx) { return static_cast<char*>(ctx->scratch) + kQueryOffset; }
 
 // ---------------------------------------------------------------- planning
 // Register-resident chunk width (32-bit words per lane) of the popcount scan.
