@@ -366,7 +366,7 @@ def bench_headline(args):
     used = BACKEND_NAMES[fid_backend_for(ctx.handle, db.handle, w.n_q)]
     roofline = roofline_for(used, comps, scan_avg_s)
     if used == "mfma_fp4" and n_refs == w.n_refs:
-        roofline["traffic"] = recorded_traffic("fp4_scan_kernel<0, 1>")
+        roofline["traffic"] = recorded_traffic("fp4_scan_kernel<1, false, 8>")
     add_measured_peak(roofline, used, None if args.no_peaks else measure_peaks(ctx))
 
     serving = None

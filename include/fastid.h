@@ -27,9 +27,13 @@
  *   - Memory: every large buffer (profiles, database, workspace, outputs) is
  *     device memory allocated and owned by the caller; the library keeps only
  *     pointers to it for the duration of a call (fid_db keeps db_mem until
- *     fid_db_destroy).  The library itself allocates only small per-context
- *     scratch (staged query words and status words), freed by
- *     fid_ctx_destroy.
+ *     fid_db_destroy).  The library itself allocates small per-context
+ *     scratch (staged query words) and the events of streamed calls, freed by
+ *     fid_ctx_destroy; one page of pinned host memory, kept until the process
+ *     ends, through which kernels tell a waiting call a verdict or a total (64
+ *     contexts share it, others get a word of their own); and at most four
+ *     copy streams per device, which streamed calls borrow and the destruction
+ *     of the device's last context frees.
  *   - Execution: work is enqueued on the context's HIP stream (borrowed, not
  *     owned) and is asynchronous unless a function says it synchronises.
  *     Results are valid once that stream has been synchronised.  A context
@@ -325,7 +329,10 @@ int fid_compare_tiles(fid_ctx* ctx, const fid_db* db, const uint64_t* q_dev, int
                       int mode, const int64_t* tiles_host, int32_t n_tiles, int32_t th,
                       int32_t tw, int32_t* out_dev);
 
-/* Workspace bytes fid_compare_topk needs for this database, n_q and k. */
+/*
+ * Workspace bytes with which fid_compare_topk takes its fastest route for this
+ * database, n_q and k (at most 200 MiB where that writes all counts).
+ */
 int fid_topk_workspace_bytes(fid_ctx* ctx, const fid_db* db, int32_t n_q, int32_t k,
                              size_t* bytes);
 
@@ -334,8 +341,12 @@ int fid_topk_workspace_bytes(fid_ctx* ctx, const fid_db* db, int32_t n_q, int32_
  * shipping C to the host): for each query the k smallest (C[q][r], r) pairs in
  * lexicographic order -- ties in count go to the lowest index -- written
  * ascending to cnt_dev[q * k + j] / idx_dev[q * k + j].  If k > N_R the tail is
- * (INT32_MAX, -1).  The full matrix is never materialised.  ws_dev: caller
- * device memory of fid_topk_workspace_bytes() bytes.  Asynchronous.
+ * (INT32_MAX, -1).  Up to 262,144 references (131,072 for the popcount
+ * scan) and 50M counts the counts are written to the workspace and selected
+ * from; larger matrices are never materialised, but filtered during the scan
+ * into lists of candidates.  ws_dev: caller device memory of
+ * fid_topk_workspace_bytes() bytes; a call given less takes the scan with
+ * lists if those fit.  Errors: FID_ENOMEM where neither does.  Asynchronous.
  */
 int fid_compare_topk(fid_ctx* ctx, const fid_db* db, const uint64_t* q_dev, int32_t n_q,
                      int mode, int32_t k, void* ws_dev, size_t ws_bytes, int32_t* cnt_dev,
@@ -350,8 +361,9 @@ int fid_compare_topk(fid_ctx* ctx, const fid_db* db, const uint64_t* q_dev, int3
  * (no hipMalloc, hipFree or allocating library routine).  The array must hold
  * the workspace of a list scan (k-slot lists and the seed's counts) plus the
  * staged queries (at most n_q x L/2 bytes + 4 n_q, 256-byte aligned): e.g. up to
- * 240 queries against 20M references at 2048 loci and k = 32.  Larger problems return FID_ENOMEM, with the bytes
- * needed in fid_last_error(), before anything is enqueued.  Every call on a
+ * 240 queries against 20M references at 2048 loci and k = 32.  Larger problems
+ * return FID_ENOMEM, with the bytes needed in fid_last_error(), before anything
+ * is enqueued.  Every call on a
  * device shares that device's array: calls that overlap on one device (two
  * streams, two contexts or two threads) race and must be ordered by the
  * caller.  Nothing in the array needs clearing between calls.  Asynchronous

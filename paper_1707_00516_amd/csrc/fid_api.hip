@@ -454,7 +454,7 @@ Plan plan_fp4(int num_cus, int64_t r_lo, int64_t r_hi, int32_t nq, int epi)
     const int64_t ntiles = (r_hi - base + fp4_refs_per_wg() - 1) / fp4_refs_per_wg();
     // A short range's 512-reference tiles leave CUs idle: more query tiles, down
     // to one block of 16, as far as there are CUs (all counts, 20k x 2048
-    // loci, 40 reference tiles: 64 queries 13.3 -> 9.7 us, 128 20.3 -> 11.3, 256
+    // loci, 40 reference tiles: 64 queries 13.3 -> 9.4 us, 128 20.3 -> 11.3, 256
     // 21.3 -> 14.3).
     n_qtiles = std::max(n_qtiles, std::min<int64_t>((nq + 15) / 16, num_cus / ntiles));
     const int64_t target = (int64_t)num_cus * env_int("FASTID_MFMA_WG_PER_CU", 2, 1, 64);

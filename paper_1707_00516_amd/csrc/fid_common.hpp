@@ -198,8 +198,8 @@ int mfma_queries_per_wg();
 int mfma_waves_per_wg();
 hipError_t launch_fp4_scan(int mode, int epi, const ScanParams& p, const MfmaBuffers& b,
                            hipStream_t s);
-// Identity queries (mode, or qmode[i] when mode is kModePerQuery) get codes of
-// both signs.
+// Identity queries (mode, or qmode[i] when mode is kModePerQuery) get
+// doubled codes.
 hipError_t launch_expand_queries_fp4(const uint64_t* q, int32_t n_q, int32_t row_words,
                                      int32_t n_loci, int mode, const int32_t* qmode, uint8_t* qx,
                                      int32_t kpad, int32_t* pcq, hipStream_t s, uint64_t* clear = nullptr);

@@ -16,8 +16,9 @@
 //     accumulate) per 32 loci;
 //   * the count is consumed in registers by the epilogue: a store (full
 //     matrix / tiles), a filter into per-worker top-k lists, or a threshold
-//     hit append; the query x reference matrix is never written for top-k or
-//     threshold output (the reduction-on-GPU Section IV proposes).
+//     hit append; threshold output and the top-k of long ranges never write
+//     the query x reference matrix (the reduction-on-GPU Section IV proposes),
+//     short ranges' counts are written and selected from.
 #include <algorithm>
 #include <type_traits>
 

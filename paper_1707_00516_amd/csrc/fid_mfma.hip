@@ -622,9 +622,9 @@ __device__ __forceinline__ uint32_t word_of(const uint4& v, int t)
 }
 
 // Query tiles: the 16-query blocks of [0, n_q) dealt evenly to a launch's
-// tiles (ceil(n_q / 128) of them, more over a short range), so that 131 queries run as tiles of 5 and 4 blocks
-// and not as 8 and 1 (whose references are read, spread and checked for
-// 3 queries).
+// tiles (ceil(n_q / 128) of them, more over a short range), so that 131 queries
+// run as tiles of 5 and 4 blocks and not as 8 and 1 (whose references are read,
+// spread and checked for 3 queries).
 __host__ __device__ inline int fp4_tile_blocks(int n_q) { return (n_q + 15) / 16; }
 __host__ __device__ inline int fp4_tile_begin(int n_q, int n_tiles, int t)
 {
