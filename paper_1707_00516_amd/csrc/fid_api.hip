@@ -138,7 +138,7 @@ constexpr int kCopyStreamsKept = 4;
 constexpr int kPoolDevices = 64;  // a device beyond these keeps none
 struct CopyPool {
     int contexts, n;
-    int64_t calls;  // that wanted a second stream
+    int64_t calls;  // that took streams
     hipStream_t idle[kCopyStreamsKept];
 };
 std::mutex g_copy_mu;
@@ -174,22 +174,25 @@ public:
     {
         {
             std::lock_guard<std::mutex> lk(g_copy_mu);
+            call_ = pool_ ? pool_->calls++ : 0;
             while (pool_ && n_ < most && pool_->n > 0) s_[n_++] = pool_->idle[--pool_->n];
         }
         for (; n_ < least; ++n_)
             FID_HIP(hipStreamCreateWithFlags(&s_[n_], hipStreamNonBlocking), "hipStreamCreate");
         return FID_OK;
     }
+    // To be called after the first block's copy has been enqueued on the first
+    // stream.  The runtime sets up another copy engine (7 ms, the host waiting)
+    // the first time that a copy finds one busy: a process's first two calls
+    // keep the second copy back until the first is done (1M x 2048 loci in eight
+    // blocks: first call 14.2 ms without, 8.3 with).
+    hipError_t first_copied() const { return call_ < 2 ? hipStreamSynchronize(s_[0]) : hipSuccess; }
     // To be called while this call's copies run: a second stream for the calls
-    // to come if this one would have used it and is not the first of its kind
-    // (without it they do as this one did).
+    // to come if this one would have used it and is not the first (without it
+    // they do as this one did).
     void grow_pool(bool wanted)
     {
-        if (!pool_ || !wanted || n_ > 1) return;
-        {
-            std::lock_guard<std::mutex> lk(g_copy_mu);
-            if (pool_->calls++ == 0) return;
-        }
+        if (!pool_ || !wanted || n_ > 1 || call_ == 0) return;
         hipStream_t s;
         if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess) give(s);
         else (void)hipGetLastError();
@@ -211,6 +214,7 @@ private:
         (void)hipStreamDestroy(s);
     }
     CopyPool* pool_;
+    int64_t call_ = 0;  // streamed calls of the process on this device before this one
     int n_ = 0;
     hipStream_t s_[2];
 };
@@ -221,8 +225,8 @@ private:
 // one stream and 4.66 on two, the copies alone 4.5; in a process that had run
 // hundreds of other calls 8.45 and 6.1).  Made before a process's first copies
 // the second stream would cost that call 8 ms, so a program's only call does
-// without it; its second call makes it while its copies run, and the third pays
-// about 4 ms for the stream's first copies.
+// without it; its second call makes it while its copies run, and the third and
+// fourth pay 5 ms each for the further copy engines that two streams meet.
 constexpr int64_t kTwoStreamBlocks = 3;
 
 }  // namespace
@@ -1490,6 +1494,7 @@ int fid_compare_topk_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
             hip(hipMemcpyAsync(stage, rows_host + r0 * rw, (size_t)n * (size_t)rw * sizeof(uint64_t),
                                hipMemcpyHostToDevice, copy.of(slot)), "block copy");
         if (!st) hip(hipEventRecord(copied[slot], copy.of(slot)), "hipEventRecord");
+        if (!st && b == 0) hip(copy.first_copied(), "hipStreamSynchronize");
         if (!st) hip(hipStreamWaitEvent(ctx->stream, copied[slot], 0), "hipStreamWaitEvent");
         if (st) break;
         fid_db* db = nullptr;
@@ -1604,6 +1609,7 @@ int fid_compare_full_streamed(fid_ctx* ctx, const uint64_t* rows_host, int64_t n
             hip(hipMemcpyAsync(stage, rows_host + r0 * rw, (size_t)n * (size_t)rw * sizeof(uint64_t),
                                hipMemcpyHostToDevice, h2d), "block copy");
         if (!st) hip(hipEventRecord(copied[slot], h2d), "hipEventRecord");
+        if (!st && b == 0) hip(copy.first_copied(), "hipStreamSynchronize");
         // build and count: the count slot is free once block b - 2's counts shipped
         if (!st) hip(hipStreamWaitEvent(ctx->stream, copied[slot], 0), "hipStreamWaitEvent");
         if (!st && b >= 2) hip(hipStreamWaitEvent(ctx->stream, shipped[slot], 0), "hipStreamWaitEvent");
@@ -1922,6 +1928,7 @@ int fid_compare_threshold_streamed(fid_ctx* ctx, const uint64_t* rows_host, int6
             hip(hipMemcpyAsync(stage[slot], rows_host + r0 * rw, (size_t)n * (size_t)rw * sizeof(uint64_t),
                                hipMemcpyHostToDevice, copy.of(slot)), "block copy");
         if (!st) hip(hipEventRecord(copied[slot], copy.of(slot)), "hipEventRecord");
+        if (!st && b == 0) hip(copy.first_copied(), "hipStreamSynchronize");
         if (!st) hip(hipStreamWaitEvent(ctx->stream, copied[slot], 0), "hipStreamWaitEvent");
         if (st) break;
         fid_db* db = nullptr;
